@@ -334,9 +334,10 @@ iobm_status iobm_grad_transmission(iobm_ctx ctx, const iobm_solve_opts* opts, in
                                    const double* E, double* T_total, void* dT_dV);
 
 /* Launch shapes of the volume kernels: a tuning knob, not part of the
- * method.  By default the first solve of a context in each precision times
- * the admissible stencil shapes and z-filter chunk lengths on its own batch
- * and keeps the fastest (the autotuner).  Shapes change the order in which
+ * method.  By default the first solve of a context in each precision (with a
+ * preconditioner other than the lateral-Fourier one, whose iteration applies
+ * no stencil) times the admissible stencil shapes on its own batch and keeps
+ * the fastest (the autotuner).  Shapes change the order in which
  * the FP64 partial sums of the COCG inner products are combined, so two
  * contexts tuned on their own may differ in the last bits (|Delta T| at the
  * solver tolerance).  Pinning the same shape in both makes them run the same
@@ -350,15 +351,18 @@ iobm_status iobm_grad_transmission(iobm_ctx ctx, const iobm_solve_opts* opts, in
  *                      block (small batches get shorter chunks, so that every
  *                      compute unit has blocks)
  *   zfilter_chunk:     lateral-Fourier preconditioner, 8, 16 or 32 planes per
- *                      chunk of the z recursion (at most 8 chunks)
- *   plane_fft:         1 = in-register plane FFT (square planes of 8, 12, 16,
- *                      24, 32 or 48 points), 2 = LDS Stockham plane FFT
+ *                      chunk of the z recursion (at most 8 chunks) in
+ *                      iobm_precondition, block COCG and the solve at a
+ *                      Bloch vector; the mode-space iteration of the other
+ *                      solves takes 8 planes always
+ *   plane_fft:         1 = in-register plane transforms (square planes of 8,
+ *                      12, 16, 24, 32 or 48 points), 2 = LDS Stockham stages
  *   rz_pass:           lateral-Fourier preconditioner with the in-register
  *                      plane FFT: the pass that forms the r^T z partials,
  *                      1 = the z filter (each mode beside its negative in one
  *                      wavefront; used where its pair blocks fit the nz
  *                      partial slots of a state), 2 = the inverse plane FFT
- *                      (the autotuner times both and keeps the faster)
+ *                      (iobm_precondition with r^T z; default 1 where it fits)
  * Shapes are kept per kernel arithmetic: IOBM_C64_REFINED selects the
  * complex64 kernels of the inner iteration, IOBM_C128 the complex128 ones
  * (including the FP64 residual refresh of a IOBM_C64_REFINED solve).
@@ -404,13 +408,16 @@ enum { IOBM_K_STENCIL = 1,      /* stencil in the iteration precision; with the
        IOBM_K_DOT = 6,          /* bilinear / norm reductions */
        IOBM_K_UPDATE = 7,       /* r -= alpha q, |r|^2 partials */
        IOBM_K_STENCIL_C128 = 8, /* stencil in complex128 (FP64 residuals) */
-       IOBM_K_FFT_PLANES = 9,   /* forward batched 2D plane FFT of the preconditioner */
-       IOBM_K_ZFILTER = 10,     /* the z recursion of the preconditioner */
-       IOBM_K_ACCUMULATE = 11,  /* x += d + alpha p, d = 0 (refinement) */
+       IOBM_K_FFT_PLANES = 9,   /* batched 2D plane transforms without a dot */
+       IOBM_K_ZFILTER = 10,     /* the z recursion of the preconditioner; in the mode-space
+                                   iteration with the residual update (read W, R, R_old;
+                                   write R, Z: 5 streams) */
+       IOBM_K_ACCUMULATE = 11,  /* the solution update of a refinement: x += d + alpha p, or
+                                   in the mode-space iteration x += inverse transform of D */
        IOBM_K_NONLOCAL_C128 = 12, /* as IOBM_K_NONLOCAL, complex128 (flops) */
        IOBM_K_FFT_PLANES_DOT = 13, /* inverse plane FFT with the r^T z partials */
-       IOBM_K_FFT_PLANES_UPD = 14, /* forward plane FFT of q with the mode-space
-                                   residual update R -= alpha FFT(q) */
+       IOBM_K_FFT_PLANES_UPD = 14, /* plane pass of the mode-space iteration, Z -> V z -> W
+                                   (2 streams; 4 with a stored direction) */
        IOBM_K_PRECOND_JACOBI = 15,  /* Jacobi preconditioner: read r, write z */
        IOBM_K_BLOCK_GRAM = 16,      /* block COCG: s x s Grams of a group (MFMA f64) + their
                                        fixed-order sum; bytes: read both blocks once */

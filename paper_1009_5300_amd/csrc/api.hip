@@ -26,7 +26,7 @@
 #include <mutex>
 #include <vector>
 
-#include "internal.h"
+#include "modal.h"
 
 // Static device workspace of iobm_precondition_noalloc: a file-scope array
 // that every GPU the library runs on holds until the process ends.  Its name
@@ -135,7 +135,7 @@ iobm_status fail(iobm_ctx ctx, iobm_status s, const std::string& msg) {
 enum Slot {
   S_B, S_XHI, S_RHI, S_Y, S_R, S_Z, S_P, S_P2, S_Q, S_D, S_PF, S_PART, S_PARTA, S_PARTZ, S_PARTR, S_PARTN, S_SCAL,
   S_IDX, S_AMP,
-  S_TR, S_KB, S_GRAD_D, S_BLK_PART, S_BLK_G, S_BLK_N2, NSLOT
+  S_TR, S_KB, S_GRAD_D, S_BLK_PART, S_BLK_G, S_BLK_N2, S_MODAL, S_FILT, NSLOT
 };
 
 void* workspace(iobm_ctx ctx, int slot, size_t bytes) {
@@ -381,13 +381,18 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   for (int i = 0; i < nb; ++i) all[i] = i;
   int* all_d = upload(ctx, S_IDX, all, 32 * 1024);
   zd* rhi = (zd*)workspace(ctx, S_RHI, (size_t)nb * vol * sizeof(zd));
+  // with the lateral-Fourier preconditioner the iteration runs in lateral
+  // mode space (modal.h): the seven vectors are then the ring of residuals
+  // (r is its slot 0), Z / W and, in complex128, the folded correction; the
+  // folded direction (and correction, in complex64) share r_hi, which is
+  // written only when a replacement has consumed them
+  const bool modal = o.precond == IOBM_PC_LATERAL_FFT;
   cplx<T>* d = (cplx<T>*)workspace(ctx, S_D, vb);
   cplx<T>* r = (cplx<T>*)workspace(ctx, S_R, vb);
   cplx<T>* pa = (cplx<T>*)workspace(ctx, S_P, vb);   // direction, two buffers used in turn
   cplx<T>* pb = (cplx<T>*)workspace(ctx, S_P2, vb);
   cplx<T>* q = (cplx<T>*)workspace(ctx, S_Q, vb);
   cplx<T>* z = o.precond == IOBM_PC_NONE ? r : (cplx<T>*)workspace(ctx, S_Z, vb);
-  cplx<T>* pf = o.precond == IOBM_PC_LATERAL_FFT ? (cplx<T>*)workspace(ctx, S_PF, vb) : nullptr;
   const int nblk = dot_blocks(ctx);
   const int nz_slots = precond_slots(ctx, o.precond);
   Partial* part = (Partial*)workspace(ctx, S_PART, (size_t)nb * nblk * sizeof(Partial));
@@ -396,14 +401,35 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
                          ? part
                          : (Partial*)workspace(ctx, S_PARTZ, (size_t)nb * nz_slots * sizeof(Partial));
   Partial* part_rn = (Partial*)workspace(ctx, S_PARTR, (size_t)nb * PQ_SLOTS * sizeof(Partial));
-  // with the lateral-Fourier preconditioner on square planes, the update runs
-  // inside its forward transform, which writes the |r|^2 partials per plane:
-  // between replacements the iterated residual lives only in lateral mode
-  // space (R = FFT(r) in pf, R -= alpha FFT(q)); the real-space r is formed
-  // only by a replacement, whose preconditioner pass transforms it into pf
-  const bool fuse_upd = o.precond == IOBM_PC_LATERAL_FFT && fft_reg_available<T>(ctx);
-  Partial* part_n2 = fuse_upd ? (Partial*)workspace(ctx, S_PARTN, (size_t)nb * ctx->g.nz * sizeof(Partial)) : part;
-  const int n2_slots = fuse_upd ? ctx->g.nz : nblk;
+  Modal<T> MD;
+  constexpr int kRing = ModalRing<T>::n;
+  if (modal) {
+    cplx<T>* vecs[7] = {r, z, pa, pb, q, d, (cplx<T>*)workspace(ctx, S_PF, vb)};
+    for (int i = 0; i < kRing; ++i) MD.ring[i] = vecs[i];
+    MD.w = vecs[6];
+    MD.fold_s = (cplx<T>*)rhi;
+    if (kRing == 6) {
+      MD.fold_t = MD.fold_s + vol;
+      MD.fold_stride = 2 * vol;
+    } else {
+      MD.fold_t = d;
+      MD.fold_stride = vol;
+    }
+    MD.nE = (int)ctx->modeE.size();
+    MD.nmb = modal_mode_blocks(ctx);
+    MD.ndp = ctx->g.nz + (ctx->kb.ncen > 0 ? 1 : 0);
+    const int nf = ctx->g.nf;
+    MD.ft = (cplx<T>*)workspace(ctx, S_FILT, (size_t)MD.nE * (3 * nf + nf * nf) * ctx->g.nxy * sizeof(cplx<T>));
+    const size_t rb = sizeof(ModalScal) + 2 * kRing * sizeof(zd) + (size_t)(MODAL_PART * MD.nmb + 2 * MD.ndp) * sizeof(double);
+    char* mp = (char*)workspace(ctx, S_MODAL, (size_t)nb * rb);
+    MD.sc = (ModalScal*)mp;
+    MD.ha = (zd*)(MD.sc + nb);
+    MD.hb = MD.ha + (size_t)nb * kRing;
+    MD.part = (double*)(MD.hb + (size_t)nb * kRing);
+    MD.dpart = MD.part + (size_t)nb * MODAL_PART * MD.nmb;
+    MD.e_rhs = e_d;
+    HIPCHK(modal_setup<T>(ctx, MD));
+  }
   // per-rhs scalars; |r|^2 and the breakdown flags are adjacent so that one
   // copy brings both to the host at a convergence check
   const size_t nb8 = ((size_t)nb + 1) & ~(size_t)1;
@@ -444,12 +470,19 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   auto precond = [&](int nact, const int* ad) {
     if (o.precond == IOBM_PC_TRUNCATED_LAPLACIAN)
       HIPCHK(launch_precond_laplacian<T>(ctx, o.alpha, r, z, nact, ad, part_rz));
-    else if (o.precond == IOBM_PC_LATERAL_FFT)
-      HIPCHK(launch_precond_fft<T>(ctx, r, z, pf, nact, e_d, modes, ad, part_rz));
     else if (o.precond == IOBM_PC_JACOBI)
       HIPCHK(launch_precond_jacobi<T>(ctx, r, z, nact, e_d, E_d, ad, part_rz));
     else
       HIPCHK(launch_dot<T>(ctx, r, r, nact, ad, part_rz));
+  };
+  // the listed rhs start over from the residual in r: p = z next
+  auto restart = [&](int n, const int* ld) {
+    if (modal) {
+      HIPCHK(modal_start<T>(ctx, MD, n, ld));
+      return;
+    }
+    precond(n, ld);
+    HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_rz, nz_slots, nullptr, 0, FIN_RESTART, n, ld));
   };
   std::vector<int> since(nb, 0);  // steps since the last replacement, per rhs (d holds data from 2 on)
   std::vector<char> kept(nb, 0);  // the last replacement kept the direction (p_old is read at its first step)
@@ -471,7 +504,14 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
     const int n = (int)lst.size();
     int nfirst = 0, ndead = 0;  // x not read (first refinement), d not read (no step since the last)
     for (int i : lst) { nfirst += out.refin[i] == 0; ndead += since[i] < 2; }
-    HIPCHK(launch_accumulate<T>(ctx, x, d, pold, alpha, xset, dlive, n, ld, nfirst, ndead));
+    if (modal) {
+      double reads = 0;  // vectors of the ring (and its fold) that make up the correction
+      for (int i : lst)
+        reads += since[i] >= modal_short_steps<T>() ? 1 : (since[i] < kRing - 1 ? since[i] : since[i] % (kRing - 1) + 2);
+      HIPCHK(modal_correct<T>(ctx, MD, x, xset, n, ld, reads, nfirst));
+    } else {
+      HIPCHK(launch_accumulate<T>(ctx, x, d, pold, alpha, xset, dlive, n, ld, nfirst, ndead));
+    }
     if (ctx->kb.ncen == 0) {
       HIPCHK(launch_refresh<T>(ctx, x, b, rhi, r, n, E_d, e_d, modes, ld, part_rn));
       HIPCHK(launch_finish2(ctx, rho, alpha, beta, tn2, flag, part_rn, PQ_SLOTS, nullptr, 0, FIN_NORM, n, ld,
@@ -517,30 +557,44 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   int nact = (int)act.size();
   int* act_d = upload(ctx, S_IDX, act, 64 * 1024);
   HIPCHK(launch_init_r<T>(ctx, b, r, nact, act_d));
-  if (!ctx->tuned[prec_index<T>()]) {
+  if (!modal && !ctx->tuned[prec_index<T>()]) {
     // the shapes are timed on the fused operator with p_old = 0 and a
     // nonzero beta (0x3F bytes: 4.8e-4), so that every stream is read
     HIPCHK(hipMemsetAsync(pa, 0, vb, ctx->stream));
     HIPCHK(hipMemsetAsync(beta, 0x3F, nb * sizeof(zd), ctx->stream));
     HIPCHK(hipMemsetAsync(alpha, 0x3F, nb * sizeof(zd), ctx->stream));  // d += alpha * 0 leaves d = 0
     ApplyFuse<T> TF{r, pa, beta, pb, part_pq, alpha, d, dlive};
-    autotune<T>(ctx, r, q, pf, nact, E_d, e_d, modes, act_d, &TF,
-                o.precond == IOBM_PC_LATERAL_FFT ? part_rz : nullptr);
+    autotune<T>(ctx, r, q, nullptr, nact, E_d, e_d, modes, act_d, &TF);
     HIPCHK(hipMemsetAsync(part_pq, 0, (size_t)nb * PQ_SLOTS * sizeof(Partial), ctx->stream));
   }
-  precond(nact, act_d);
-  HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_rz, nz_slots, nullptr, 0, FIN_RESTART, nact, act_d));
+  restart(nact, act_d);
 
   // One iteration is three passes over the batch:
   //   operator:  p_new = z + beta p_old, q = A p_new, partials of p_new^T q
   //   update:    d += alpha p_new, r -= alpha q, partials of |r|^2 (and r^T r)
-  //              (fused: inside the preconditioner's forward transform, on
-  //              R = FFT(r) from FFT(q))
   //   precond:   z = P r, partials of r^T z
-  // with the scalar steps (alpha; beta, rho, |r|^2) in between.
+  // with the scalar steps (alpha; beta, rho, |r|^2) in between; with the
+  // lateral-Fourier preconditioner two passes in mode space (modal.h).
   // one check's iterations, launched one by one or captured into a graph
   CheckGraph cg;
   auto enqueue_check = [&]() {
+    if (modal) {
+      for (int k = 0; k < check; ++k) {
+        constexpr int kShort = modal_short_steps<T>();
+        ModalPlan plan;
+        for (int i : act) {
+          const int n = since[i] + k;  // steps before this one
+          plan.fastp = plan.fastp || n < kShort;
+          plan.slowp = plan.slowp || n >= kShort;
+          plan.fold = plan.fold || (n < kShort && (n + 1) % (kRing - 1) == 0);
+          plan.turn = plan.turn || n + 1 == kShort;
+        }
+        if (graphs) plan.fastp = plan.slowp = plan.fold = plan.turn = true;  // a captured sequence covers any count
+        HIPCHK(modal_step<T>(ctx, MD, nact, act_d, plan));
+      }
+      HIPCHK(modal_check<T>(ctx, MD, nact, act_d, rn2, flag));
+      return;
+    }
     for (int k = 0; k < check; ++k) {
       int nfresh = 0, nfirstd = 0, nkept = 0;  // byte count only: steps since the replacement 0 and 1
       for (int i : act) {
@@ -552,16 +606,9 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
       HIPCHK(launch_apply<T>(ctx, nullptr, q, nact, E_d, e_d, modes, act_d, &F));
       HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_pq, PQ_SLOTS, nullptr, 0, FIN_ALPHA, nact, act_d,
                             nullptr, dlive));
-      if (fuse_upd) {
-        FftUpd<T> U;
-        U.q = q; U.alpha = alpha; U.n2part = part_n2;
-        HIPCHK(launch_precond_fft<T>(ctx, r, z, pf, nact, e_d, modes, act_d, part_rz, &U));
-      } else {
-        HIPCHK(launch_update_r<T>(ctx, r, q, alpha, nact, act_d, part));
-        if (o.precond != IOBM_PC_NONE) precond(nact, act_d);  // P = I: r^T r came with the update
-      }
-      HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_rz, nz_slots, part_n2, n2_slots, FIN_BETA, nact,
-                            act_d));
+      HIPCHK(launch_update_r<T>(ctx, r, q, alpha, nact, act_d, part));
+      if (o.precond != IOBM_PC_NONE) precond(nact, act_d);  // P = I: r^T r came with the update
+      HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_rz, nz_slots, part, nblk, FIN_BETA, nact, act_d));
       std::swap(pold, pnew);
     }
   };
@@ -597,14 +644,14 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
       cg.nact = nact;
       cg.act = act_d;
       cg.pold = p0;
-      if (check % 2) std::swap(pold, pnew);  // capture swapped them on the host: back to the launch state
+      if (!modal && check % 2) std::swap(pold, pnew);  // capture swapped them on the host: back to the launch state
     }
     HIPCHK(hipEventRecord(ctx->cap_ev[0], ctx->stream));
     HIPCHK(hipStreamWaitEvent(ctx->cap_stream, ctx->cap_ev[0], 0));
     HIPCHK(hipGraphLaunch(cg.exec, ctx->cap_stream));
     HIPCHK(hipEventRecord(ctx->cap_ev[1], ctx->cap_stream));
     HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->cap_ev[1], 0));
-    if (check % 2) std::swap(pold, pnew);
+    if (!modal && check % 2) std::swap(pold, pnew);
   };
   while (nact > 0) {
     run_check();
@@ -656,8 +703,8 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
       if (nc > 0) {
         // z = P r of the replaced residual, rho = r^T z; a restart sets beta = 0
         // (p_new = z next), a kept direction beta = rho' / rho (p_new = z + beta p)
-        precond(nc, ld);
-        if (nr) HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_rz, nz_slots, nullptr, 0, FIN_RESTART, nr, ld));
+        if (nr) restart(nr, ld);
+        if (nk) precond(nk, ld + nr);
         if (nk) HIPCHK(launch_finish2(ctx, rho, alpha, beta, rn2, flag, part_rz, nz_slots, nullptr, 0, FIN_KEEP, nk, ld + nr));
       }
       act.assign(lists.begin() + nc, lists.end());
@@ -684,7 +731,8 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
         else if (decay[i] < 0.0) n = (int)std::min<double>(kMaxCheck, ceil(log(target / obs_r2[i]) / decay[i]));
         hist[std::max(1, std::min(kMaxCheck, n))]++;
       }
-      const double it_bytes = (lowp ? 112.0 : 224.0) * nact * (double)vol;  // one iteration's vector streams
+      // one iteration's vector streams: 14, or 7 in mode space
+      const double it_bytes = (modal ? 7.0 : 14.0) * sizeof(cplx<T>) * nact * (double)vol;
       const double s_rel = kCheckSeconds / (it_bytes / kStreamBytesPerSecond);
       double best_rate = -1;
       for (int c = 1; c <= kMaxCheck; ++c) {
@@ -1631,7 +1679,7 @@ iobm_status iobm_destroy(iobm_ctx ctx) {
     if (e.first) (void)hipFree(e.first);
   void* ptrs[] = {ctx->twx_d, ctx->twy_d, ctx->twx_f, ctx->twy_f, ctx->V_d, ctx->V_f, ctx->modes_d, ctx->sig_d,
                   ctx->sig_f, ctx->mode_flags_d, ctx->sdiag_d,
-                  ctx->kb.uvox, ctx->kb.Bd, ctx->kb.Bf, ctx->kb.Btd, ctx->kb.Btf, ctx->kb.ctile, ctx->kb.prange,
+                  ctx->kb.uvox, ctx->kb.Bd, ctx->kb.Bf, ctx->kb.Btd, ctx->kb.Btf, ctx->kb.ctile, ctx->kb.uplane, ctx->kb.prange,
                   ctx->kb.hD, ctx->kb.diag_d, ctx->arena_d};
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->arena_h) (void)hipHostFree(ctx->arena_h);
@@ -1775,6 +1823,10 @@ iobm_status iobm_set_nonlocal(iobm_ctx ctx, int32_t ncen, int32_t rank, const in
         r[0] = std::min(r[0], p);
         r[1] = std::max(r[1], p + 1);
       }
+  // first union voxel of each plane (the union is sorted by voxel id)
+  std::vector<int> uplane(ctx->g.nz + 1);
+  for (int z = 0; z <= ctx->g.nz; ++z)
+    uplane[z] = (int)(std::lower_bound(uvox.begin(), uvox.end(), z * ctx->g.nxy) - uvox.begin());
   // diagonal of B h^3 D B^T per voxel (zero off the supports)
   std::vector<double> kdiag(nu > 0 ? (size_t)ctx->g.npts : 0, 0.0);
   for (int u = 0; u < nu; ++u) {
@@ -1785,7 +1837,7 @@ iobm_status iobm_set_nonlocal(iobm_ctx ctx, int32_t ncen, int32_t rank, const in
   }
   try {
     stream_sync(ctx);
-    void* old[] = {kb.uvox, kb.Bd, kb.Bf, kb.Btd, kb.Btf, kb.ctile, kb.prange, kb.hD, kb.diag_d};
+    void* old[] = {kb.uvox, kb.Bd, kb.Bf, kb.Btd, kb.Btf, kb.ctile, kb.uplane, kb.prange, kb.hD, kb.diag_d};
     for (void* p : old)
       if (p) (void)hipFree(p);
     kb = KBData();
@@ -1796,6 +1848,7 @@ iobm_status iobm_set_nonlocal(iobm_ctx ctx, int32_t ncen, int32_t rank, const in
     HIPCHK(hipMalloc(&kb.Btd, Bt.size() * sizeof(double)));
     HIPCHK(hipMalloc(&kb.Btf, Btf.size() * sizeof(float)));
     HIPCHK(hipMalloc(&kb.ctile, ctile.size() * sizeof(int)));
+    HIPCHK(hipMalloc(&kb.uplane, uplane.size() * sizeof(int)));
     HIPCHK(hipMalloc(&kb.prange, prange.size() * sizeof(int)));
     HIPCHK(hipMalloc(&kb.hD, hD.size() * sizeof(double)));
     HIPCHK(hipMemcpy(kb.uvox, uvox.data(), nu * sizeof(int), hipMemcpyHostToDevice));
@@ -1804,6 +1857,7 @@ iobm_status iobm_set_nonlocal(iobm_ctx ctx, int32_t ncen, int32_t rank, const in
     HIPCHK(hipMemcpy(kb.Btd, Bt.data(), Bt.size() * sizeof(double), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(kb.Btf, Btf.data(), Btf.size() * sizeof(float), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(kb.ctile, ctile.data(), ctile.size() * sizeof(int), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(kb.uplane, uplane.data(), uplane.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(kb.prange, prange.data(), prange.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(kb.hD, hD.data(), hD.size() * sizeof(double), hipMemcpyHostToDevice));
     HIPCHK(hipMalloc(&kb.diag_d, kdiag.size() * sizeof(double)));

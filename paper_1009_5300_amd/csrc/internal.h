@@ -50,6 +50,7 @@ struct KBData {
   double* Btd = nullptr;  // [nproj][nu] the same values transposed (back-projection)
   float* Btf = nullptr;
   int* ctile = nullptr;   // [chunks of 64 union voxels] bit t: projector tile t has a nonzero value there
+  int* uplane = nullptr;  // [nz + 1] first union voxel of each plane
   int* prange = nullptr;  // [blocks of 256 union voxels][2] projectors [lo, hi) with nonzero values there
   double* hD = nullptr;   // [nproj][nproj] block-diagonal h^3 D (device)
   double* diag_d = nullptr;  // [npts] diagonal of B h^3 D B^T (device; Jacobi preconditioner)
@@ -278,23 +279,14 @@ hipError_t launch_rhs(iobm_ctx c, int nrhs, const int* e_rhs, const int* mode_rh
 hipError_t launch_readout(iobm_ctx c, int nrhs, int side, const zd* x, const ModeData* modes, const int* e_rhs,
                           zd* amp_near, zd* amp_far);
 int dot_blocks(iobm_ctx c);
-// The COCG residual update fused into the preconditioner's forward transform
-// (square planes of the register FFT only, see fft_reg_available): the
-// residual, kept in lateral mode space in the preconditioner's scratch
-// (R = FFT(r)), is updated from q, R -= alpha FFT(q).  The per-plane partials
-// of |r|^2 go to n2part[rhs][nz].
-template <typename T>
-struct FftUpd {
-  const cplx<T>* q = nullptr;
-  const zd* alpha = nullptr;
-  Partial* n2part = nullptr;
-};
+// whether the plane transforms of this context run in registers (square planes
+// of the fixed list, unless the launch shape names the LDS path)
 template <typename T>
 bool fft_reg_available(iobm_ctx c);
 template <typename T>
 hipError_t launch_precond_fft(iobm_ctx c, const cplx<T>* r, cplx<T>* z, cplx<T>* scratch,
                               int nrhs, const int* e_rhs, const ModeData* modes,
-                              const int* active, Partial* dpart = nullptr, const FftUpd<T>* upd = nullptr);
+                              const int* active, Partial* dpart = nullptr);
 int precond_slots(iobm_ctx c, int precond);
 template <typename T>
 hipError_t launch_kb_apply(iobm_ctx c, const cplx<T>* x, cplx<T>* y, int nrhs, Partial* pq_part,

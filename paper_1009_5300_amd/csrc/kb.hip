@@ -30,7 +30,7 @@
 // a mask of the nonzero projector tiles, per 256-voxel block the range of
 // nonzero projectors (both set with the projectors) bound the work; what is
 // skipped is exactly zero.
-#include "internal.h"
+#include "modal.h"
 
 namespace {
 
@@ -187,10 +187,12 @@ __global__ void __launch_bounds__(64 * KB_WAVES) k_kb_project(KBData kb, long lo
 // Sum the voxel-split partials in fixed order (each thread a strided subset
 // of the splits, then the subsets in order), then W = (h^3 D) C in FP64
 // over the centre's own rank x rank block.  With pq set, also the nonlocal
-// part of x^T (A x), which is -C^T W, to pq[rhs][PQ_KB].
+// part of x^T (A x), which is -C^T W, to pq[rhs][PQ_KB]; with dz set, C^T W
+// (x^T V_NL x) to dz[rhs dzs] (re, im).
 __global__ void __launch_bounds__(256) k_kb_scale(KBData kb, int nact, int ksplit, const double* __restrict__ part,
                                                   double* __restrict__ W, Partial* __restrict__ pq,
-                                                  const int* __restrict__ active) {
+                                                  const int* __restrict__ active, double* __restrict__ dz,
+                                                  long long dzs) {
   const int slot = blockIdx.x;
   const int nv = 2 * kb.nproj_pad;  // values per right-hand side (re, im per projector)
   const int nsl = 256 / nv;         // >= 1: nproj_pad <= 128
@@ -222,7 +224,7 @@ __global__ void __launch_bounds__(256) k_kb_scale(KBData kb, int nact, int kspli
     W[(long long)slot * nv + t] = acc;
     Wsh[t] = acc;
   }
-  if (!pq) return;
+  if (!pq && !dz) return;
   __syncthreads();
   if (t == 0) {
     double re = 0, im = 0;
@@ -230,9 +232,15 @@ __global__ void __launch_bounds__(256) k_kb_scale(KBData kb, int nact, int kspli
       re -= C[2 * q] * Wsh[2 * q] - C[2 * q + 1] * Wsh[2 * q + 1];
       im -= C[2 * q] * Wsh[2 * q + 1] + C[2 * q + 1] * Wsh[2 * q];
     }
-    Partial P;
-    P.re = re; P.im = im; P.n2 = 0; P.pad = 0;
-    pq[(long long)(active ? active[slot] : slot) * PQ_SLOTS + PQ_KB] = P;
+    const long long rhs = active ? active[slot] : slot;
+    if (dz) {
+      dz[rhs * dzs] = -re;
+      dz[rhs * dzs + 1] = -im;
+    } else {
+      Partial P;
+      P.re = re; P.im = im; P.n2 = 0; P.pad = 0;
+      pq[rhs * PQ_SLOTS + PQ_KB] = P;
+    }
   }
 }
 
@@ -308,6 +316,10 @@ hipError_t launch_project(const KBData& kb, hipStream_t s, long long vol, int na
 
 }  // namespace
 
+template <typename T> static const T* btmat_host(const KBData& kb);
+template <> const double* btmat_host<double>(const KBData& kb) { return kb.Btd; }
+template <> const float* btmat_host<float>(const KBData& kb) { return kb.Btf; }
+
 // Voxel splits of the projection: about 192 union voxels each, at most 128.
 static int kb_ksplit(const KBData& kb) {
   int s = (kb.nu + 191) / 192;
@@ -323,10 +335,11 @@ size_t kb_proj_bytes(iobm_ctx c, int nrhs) {
   return part + W;
 }
 
+// The projection and the scaled sums W[slot][2 npad] (in the context's
+// scratch), with the partial of the bilinear form to pq or dz (k_kb_scale).
 template <typename T>
-hipError_t launch_kb_apply(iobm_ctx c, const cplx<T>* x, cplx<T>* y, int nrhs, Partial* pq_part,
-                           const int* active) {
-  if (nrhs <= 0) return hipSuccess;
+static hipError_t kb_sums(iobm_ctx c, const cplx<T>* x, int nrhs, Partial* pq_part, const int* active, double* dz,
+                          long long dzs, const double** Wout) {
   const KBData& kb = c->kb;
   const int ks = kb_ksplit(kb);
   // split length in whole chunks; trailing splits may be empty (zero partials)
@@ -351,14 +364,40 @@ hipError_t launch_kb_apply(iobm_ctx c, const cplx<T>* x, cplx<T>* y, int nrhs, P
   // algorithmic flops of the real GEMM: M = projectors, N = 2 nrhs, K = support
   prof_stop(c, rec, 2.0 * kb.nproj * (2.0 * nrhs) * kb.nu);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_kb_scale, dim3(nrhs), dim3(256), 0, c->stream, kb, nrhs, ks, part, W, pq_part, active);
-  err = hipGetLastError();
+  hipLaunchKernelGGL(k_kb_scale, dim3(nrhs), dim3(256), 0, c->stream, kb, nrhs, ks, part, W, pq_part, active, dz, dzs);
+  *Wout = W;
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_kb_apply(iobm_ctx c, const cplx<T>* x, cplx<T>* y, int nrhs, Partial* pq_part,
+                           const int* active) {
+  if (nrhs <= 0) return hipSuccess;
+  const KBData& kb = c->kb;
+  const double* W = nullptr;
+  const hipError_t err = kb_sums<T>(c, x, nrhs, pq_part, active, nullptr, 0, &W);
   if (err != hipSuccess) return err;
   dim3 gb((kb.nu + 255) / 256, (nrhs + KB_BACK_RHS - 1) / KB_BACK_RHS);
   hipLaunchKernelGGL(k_kb_back<T>, gb, dim3(256), (size_t)KB_BACK_RHS * kb.nproj_pad * sizeof(cplx<T>), c->stream,
                      kb, c->g.npts, nrhs, W, y, active);
   return hipGetLastError();
 }
+
+template <typename T>
+hipError_t launch_kb_coeffs(iobm_ctx c, const cplx<T>* x, int nrhs, const int* active, double* dz, long long dzs,
+                            KBPlane<T>* out) {
+  const KBData& kb = c->kb;
+  const hipError_t err = kb_sums<T>(c, x, nrhs, nullptr, active, dz, dzs, &out->W);
+  out->nu = kb.nu;
+  out->npad = kb.nproj_pad;
+  out->uvox = kb.uvox;
+  out->uplane = kb.uplane;
+  out->prange = kb.prange;
+  out->Bt = btmat_host<T>(kb);
+  return err;
+}
+template hipError_t launch_kb_coeffs<double>(iobm_ctx, const zd*, int, const int*, double*, long long, KBPlane<double>*);
+template hipError_t launch_kb_coeffs<float>(iobm_ctx, const zf*, int, const int*, double*, long long, KBPlane<float>*);
 
 template hipError_t launch_kb_apply<double>(iobm_ctx, const zd*, zd*, int, Partial*, const int*);
 template hipError_t launch_kb_apply<float>(iobm_ctx, const zf*, zf*, int, Partial*, const int*);

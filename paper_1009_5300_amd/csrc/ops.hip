@@ -952,13 +952,7 @@ __global__ void __launch_bounds__(256) k_fft_planes(FFTPlan2D plan, int nz, cons
 //   sum_x r(x) out(x) = scale * sum_k R(-k) in(k),   R = forward FFT of r = mvec,
 // from loads issued together with those of the input (a real-space dot
 // would read r after the transforms, with its latency exposed).
-// With MODE = FFT_UPDATE (the forward transform of the preconditioner in the
-// COCG step), the residual is kept in lateral mode space, R = FFT(r): the
-// block transforms in = q and updates out = R in place, R -= alpha FFT(q),
-// and writes the per-plane partials of |r|^2 = |R|^2 / Nxy (Parseval) to
-// dpart[rhs][z].  The real-space r is neither read nor written, and the
-// transform of the preconditioner comes with the update.
-enum { FFT_PLAIN = 0, FFT_DOT = 1, FFT_UPDATE = 2 };
+enum { FFT_PLAIN = 0, FFT_DOT = 1 };
 
 // Threads per row of the register FFT: complex128 rows of 24 points and more
 // take two threads, each holding half a row (a whole 48-point complex128 row
@@ -1008,7 +1002,7 @@ __global__ void __launch_bounds__((fft_split<T, N>() * N * PPB))
                                                            const cplx<T>* __restrict__ tw, int sign, T scale,
                                                            const int* __restrict__ active,
                                                            const cplx<T>* __restrict__ mvec,
-                                                           Partial* __restrict__ dpart, FftUpd<T> U) {
+                                                           Partial* __restrict__ dpart) {
   constexpr bool DOT = MODE == FFT_DOT;
   typedef typename Pair<T>::type VT;
   constexpr int PE = Pair<T>::n;          // elements per vector access
@@ -1035,9 +1029,6 @@ __global__ void __launch_bounds__((fft_split<T, N>() * N * PPB))
     poff[q] = (long long)prhs[q] * vol + (long long)z * NN;
   }
   VT buf[EPT];
-  cplx<T> al[PPB];  // alpha of each plane's rhs (FFT_UPDATE)
-#pragma unroll
-  for (int q = 0; q < PPB; ++q) al[q] = (MODE == FFT_UPDATE && pok[q]) ? cvt<T>(U.alpha[prhs[q]]) : mk<T>(0, 0);
   double ds_re[PPB], ds_im[PPB];
 #pragma unroll
   for (int q = 0; q < PPB; ++q) ds_re[q] = ds_im[q] = 0;
@@ -1098,13 +1089,6 @@ __global__ void __launch_bounds__((fft_split<T, N>() * N * PPB))
       }
     }
     __syncthreads();
-  } else if constexpr (MODE == FFT_UPDATE) {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int v = threadIdx.x + e * BLK;
-      const int q = v / (NN / PE), w = v - q * (NN / PE);
-      if (v < NV && pok[q]) buf[e] = reinterpret_cast<const VT*>(in + poff[q])[w];
-    }
   } else {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
@@ -1132,55 +1116,21 @@ __global__ void __launch_bounds__((fft_split<T, N>() * N * PPB))
   __syncthreads();
   lds_line_fft<T, N, SPLIT>(&sm[pl][0][li], N + 1, half, tw, tw2, sign, scale);  // column li
   __syncthreads();
-  if constexpr (MODE == FFT_UPDATE) {
-    // R -= alpha FFT(q), the old R loaded in two batches
-    constexpr int H = (EPT + 1) / 2;
 #pragma unroll
-    for (int b0 = 0; b0 < EPT; b0 += H) {
-      VT ro[H];
+  for (int e = 0; e < EPT; ++e) {
+    const int vv = threadIdx.x + e * BLK;
+    const int q = vv / (NN / PE), w = vv - q * (NN / PE);
+    if (vv < NV && pok[q]) {
+      VT o;
 #pragma unroll
-      for (int e = 0; e < H; ++e) {
-        const int vv = threadIdx.x + (b0 + e) * BLK;
-        const int q = vv / (NN / PE), w = vv - q * (NN / PE);
-        if (b0 + e < EPT && vv < NV && pok[q]) ro[e] = reinterpret_cast<const VT*>(out + poff[q])[w];
+      for (int k = 0; k < PE; ++k) {
+        const int el = w * PE + k;
+        Pair<T>::set(o, k, sm[q][el / N][el % N]);
       }
-#pragma unroll
-      for (int e = 0; e < H; ++e) {
-        const int vv = threadIdx.x + (b0 + e) * BLK;
-        const int q = vv / (NN / PE), w = vv - q * (NN / PE);
-        if (b0 + e < EPT && vv < NV && pok[q]) {
-#pragma unroll
-          for (int k = 0; k < PE; ++k) {
-            const int el = w * PE + k;
-#pragma unroll
-            for (int qq = 0; qq < PPB; ++qq)
-              if (qq == q) {
-                const cplx<T> ck = Pair<T>::get(ro[e], k) - al[qq] * sm[q][el / N][el % N];
-                Pair<T>::set(ro[e], k, ck);
-                ds_re[qq] += (double)ck.re * ck.re + (double)ck.im * ck.im;
-              }
-          }
-          reinterpret_cast<VT*>(out + poff[q])[w] = ro[e];
-        }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int vv = threadIdx.x + e * BLK;
-      const int q = vv / (NN / PE), w = vv - q * (NN / PE);
-      if (vv < NV && pok[q]) {
-        VT o;
-#pragma unroll
-        for (int k = 0; k < PE; ++k) {
-          const int el = w * PE + k;
-          Pair<T>::set(o, k, sm[q][el / N][el % N]);
-        }
-        reinterpret_cast<VT*>(out + poff[q])[w] = o;
-      }
+      reinterpret_cast<VT*>(out + poff[q])[w] = o;
     }
   }
-  if constexpr (MODE != FFT_PLAIN) {
+  if constexpr (DOT) {
 #pragma unroll
     for (int q = 0; q < PPB; ++q) {
       double a = ds_re[q], b = ds_im[q];
@@ -1189,11 +1139,7 @@ __global__ void __launch_bounds__((fft_split<T, N>() * N * PPB))
         const int gp = g0 + q;
         const int slot = gp / nz, z = gp - slot * nz;
         Partial P;
-        if (DOT) {
-          P.re = (double)scale * a; P.im = (double)scale * b; P.n2 = 0;
-        } else {
-          P.re = 0; P.im = 0; P.n2 = a / NN;  // |r|^2 of the updated residual
-        }
+        P.re = (double)scale * a; P.im = (double)scale * b; P.n2 = 0;
         P.pad = 0;
         dpart[(long long)rhs_of(active, slot) * nz + z] = P;
       }
@@ -2144,19 +2090,15 @@ hipError_t launch_sigma_diag(iobm_ctx c, int nE) {
 
 template <typename T, int N, int PPB>
 static void launch_fft_reg(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int sign, double scale, int nrhs,
-                           const int* active, const cplx<T>* mvec, Partial* dpart, const FftUpd<T>* upd) {
+                           const int* active, const cplx<T>* mvec, Partial* dpart) {
   const int nplanes = nrhs * c->g.nz;
   const dim3 grid((nplanes + PPB - 1) / PPB), blk(fft_split<T, N>() * N * PPB);
-  const FftUpd<T> U = upd ? *upd : FftUpd<T>();
-  if (upd)
-    hipLaunchKernelGGL((k_fft_planes_reg<T, N, PPB, FFT_UPDATE>), grid, blk, 0, c->stream, c->g.nz, nplanes, in, out,
-                       twx<T>(c), sign, (T)scale, active, mvec, dpart, U);
-  else if (dpart)
+  if (dpart)
     hipLaunchKernelGGL((k_fft_planes_reg<T, N, PPB, FFT_DOT>), grid, blk, 0, c->stream, c->g.nz, nplanes, in, out,
-                       twx<T>(c), sign, (T)scale, active, mvec, dpart, U);
+                       twx<T>(c), sign, (T)scale, active, mvec, dpart);
   else
     hipLaunchKernelGGL((k_fft_planes_reg<T, N, PPB, FFT_PLAIN>), grid, blk, 0, c->stream, c->g.nz, nplanes, in, out,
-                       twx<T>(c), sign, (T)scale, active, mvec, dpart, U);
+                       twx<T>(c), sign, (T)scale, active, mvec, dpart);
 }
 
 static bool square_reg_size(iobm_ctx c) {
@@ -2178,15 +2120,15 @@ template bool fft_reg_available<double>(iobm_ctx);
 
 template <typename T>
 static bool fft_reg_dispatch(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int sign, double scale, int nrhs,
-                             const int* active, const cplx<T>* mvec, Partial* dpart, const FftUpd<T>* upd) {
+                             const int* active, const cplx<T>* mvec, Partial* dpart) {
   if (!fft_reg_available<T>(c)) return false;
   switch (c->g.nx) {
-    case 8: launch_fft_reg<T, 8, 16>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd); return true;
-    case 12: launch_fft_reg<T, 12, 8>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd); return true;
-    case 16: launch_fft_reg<T, 16, 8>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd); return true;
-    case 24: launch_fft_reg<T, 24, 4>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd); return true;
-    case 32: launch_fft_reg<T, 32, 4>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd); return true;
-    default: launch_fft_reg<T, 48, 1>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd); return true;
+    case 8: launch_fft_reg<T, 8, 16>(c, in, out, sign, scale, nrhs, active, mvec, dpart); return true;
+    case 12: launch_fft_reg<T, 12, 8>(c, in, out, sign, scale, nrhs, active, mvec, dpart); return true;
+    case 16: launch_fft_reg<T, 16, 8>(c, in, out, sign, scale, nrhs, active, mvec, dpart); return true;
+    case 24: launch_fft_reg<T, 24, 4>(c, in, out, sign, scale, nrhs, active, mvec, dpart); return true;
+    case 32: launch_fft_reg<T, 32, 4>(c, in, out, sign, scale, nrhs, active, mvec, dpart); return true;
+    default: launch_fft_reg<T, 48, 1>(c, in, out, sign, scale, nrhs, active, mvec, dpart); return true;
   }
 }
 
@@ -2196,18 +2138,16 @@ static bool fft_reg_dispatch(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int si
 template <typename T>
 hipError_t launch_fft_planes(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int sign, double scale, int nrhs,
                              const int* active, const cplx<T>* dvec = nullptr, const cplx<T>* mvec = nullptr,
-                             Partial* dpart = nullptr, const FftUpd<T>* upd = nullptr) {
+                             Partial* dpart = nullptr) {
   if (nrhs <= 0) return hipSuccess;
-  if (upd && !fft_reg_available<T>(c)) return hipErrorInvalidValue;
-  const int rec = prof_start(c, upd ? IOBM_K_FFT_PLANES_UPD : (dpart ? IOBM_K_FFT_PLANES_DOT : IOBM_K_FFT_PLANES));
-  if (!fft_reg_dispatch<T>(c, in, out, sign, scale, nrhs, active, mvec, dpart, upd)) {
+  const int rec = prof_start(c, dpart ? IOBM_K_FFT_PLANES_DOT : IOBM_K_FFT_PLANES);
+  if (!fft_reg_dispatch<T>(c, in, out, sign, scale, nrhs, active, mvec, dpart)) {
     size_t sh = 2 * (size_t)c->g.nxy * sizeof(cplx<T>);
     hipLaunchKernelGGL(k_fft_planes<T>, dim3(nrhs * c->g.nz), dim3(256), sh, c->stream, c->plan, c->g.nz, in, out,
                        twx<T>(c), twy<T>(c), sign, (T)scale, active, dvec, dpart);
   }
-  // streams: plain 2; with the dot 3 (read Z, R; write z); with the update 3
-  // (read q, R; write R)
-  prof_stop(c, rec, (upd ? 3.0 : (dpart ? 3.0 : 2.0)) * nrhs * c->g.npts * sizeof(cplx<T>));
+  // streams: plain 2; with the dot 3 (read Z, R; write z)
+  prof_stop(c, rec, (dpart ? 3.0 : 2.0) * nrhs * c->g.npts * sizeof(cplx<T>));
   return hipGetLastError();
 }
 
@@ -2273,15 +2213,12 @@ static int zfilter_chunk(iobm_ctx c) {
 
 template <typename T>
 hipError_t launch_precond_fft(iobm_ctx c, const cplx<T>* r, cplx<T>* z, cplx<T>* scratch, int nrhs,
-                              const int* e_rhs, const ModeData* modes, const int* active, Partial* dpart,
-                              const FftUpd<T>* upd) {
+                              const int* e_rhs, const ModeData* modes, const int* active, Partial* dpart) {
   if (nrhs <= 0) return hipSuccess;
   const int L = zfilter_chunk<T>(c);
   if ((c->g.nz + L - 1) / L > 8) return hipErrorInvalidValue;
   const int rec = prof_start(c, IOBM_K_PRECOND_FFT);
-  // with upd, scratch holds the residual in mode space and is updated from q
-  hipError_t err = launch_fft_planes<T>(c, upd ? upd->q : r, scratch, -1, 1.0, nrhs, active, nullptr, nullptr,
-                                        upd ? upd->n2part : nullptr, upd);
+  hipError_t err = launch_fft_planes<T>(c, r, scratch, -1, 1.0, nrhs, active);
   const bool zdot = dpart != nullptr && zfilter_dot_ok<T>(c);
   if (err == hipSuccess) err = launch_zfilter<T>(c, L, scratch, z, nrhs, e_rhs, modes, active, zdot ? dpart : nullptr);
   if (err == hipSuccess && zdot) err = launch_fft_planes<T>(c, z, z, +1, 1.0 / c->g.nxy, nrhs, active);
@@ -2377,9 +2314,9 @@ template hipError_t launch_apply<float>(iobm_ctx, const zf*, zf*, int, const dou
 template hipError_t launch_precond_laplacian<double>(iobm_ctx, double, const zd*, zd*, int, const int*, Partial*);
 template hipError_t launch_precond_laplacian<float>(iobm_ctx, double, const zf*, zf*, int, const int*, Partial*);
 template hipError_t launch_precond_fft<double>(iobm_ctx, const zd*, zd*, zd*, int, const int*,
-                                               const ModeData*, const int*, Partial*, const FftUpd<double>*);
+                                               const ModeData*, const int*, Partial*);
 template hipError_t launch_precond_fft<float>(iobm_ctx, const zf*, zf*, zf*, int, const int*,
-                                              const ModeData*, const int*, Partial*, const FftUpd<float>*);
+                                              const ModeData*, const int*, Partial*);
 
 bool launch_shape_valid(iobm_ctx c, int prec, const iobm_launch_shape& s, std::string& why) {
   (void)prec;

@@ -1,0 +1,72 @@
+"""The mode-space iteration of the lateral-Fourier preconditioner at the edges
+of its kernels: plane counts around the chunk of 8 planes and around the
+changes of the mode-block width (64 and 128 planes), every register plane
+size and the LDS one, rectangular and odd planes, the nonlocal term, and
+systems that need more steps than the ring of residuals and the short
+recurrence hold.  psi is checked in the oracle's own system: its residual is
+at most 10 tol ||b|| (the solver stops at tol = 1e-10 on its own FP64 residual
+of the same system; the two evaluations differ by FP64 rounding, some 1e-13 of
+||b||)."""
+import numpy as np
+import pytest
+
+import oracle as O
+from workloads import Grid
+from workloads.synth import _kb_projectors
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _potential(g, depth, rng):
+    """Gaussian wells of the given depth along the axis over a weak random field."""
+    k, j, i = np.meshgrid(np.arange(g.nz), np.arange(g.ny), np.arange(g.nx), indexing="ij")
+    V = 0.02 * rng.uniform(-1, 1, g.shape)
+    for f in (0.3, 0.7):
+        r2 = (((i - g.nx / 2) * g.hx) ** 2 + ((j - g.ny / 2) * g.hy) ** 2 + ((k - f * g.nz) * g.hz) ** 2)
+        V -= depth * np.exp(-r2 / (2 * 1.5 ** 2))
+    return V
+
+
+CASES = [(8, 8, nz, nf, 0.2, 0) for nf, nz in ((1, 2), (2, 4), (3, 7), (2, 8), (2, 9), (2, 64), (1, 65), (2, 128),
+                                               (2, 129), (1, 256))]
+CASES += [(n, n, 10, 2, 0.2, 0) for n in (12, 16, 24, 32)]
+CASES += [(9, 6, 33, 3, 0.2, 0), (21, 10, 17, 2, 0.2, 0)]
+CASES += [(8, 8, 40, 2, 0.6, 4), (10, 9, 30, 1, 0.6, 3), (8, 8, 72, 1, 1.6, 0)]  # nonlocal; many steps
+
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["c128", "c64"])
+@pytest.mark.parametrize("nx,ny,nz,nf,depth,rank", CASES)
+def test_psi_solves_the_oracles_system(torch, nx, ny, nz, nf, depth, rank, precision):
+    from paper_1009_5300_amd import iobm
+    g = Grid(nx, ny, nz, 0.45, nf, hz_=0.5)
+    rng = np.random.default_rng(nx + 7 * ny + 31 * nz + nf)
+    V = _potential(g, depth, rng)
+    nl = None
+    if rank:
+        centres = [np.array([g.nx * g.hx / 2, g.ny * g.hy / 2, f * g.nz * g.hz]) for f in (0.3, 0.7)]
+        nl = _kb_projectors(g, centres, 0.6, rank, rng)
+    P = O.Problem(g, V, nl)
+    s = iobm.Solver(g.nx, g.ny, g.nz, g.spacings, g.nf)
+    s.set_potential(V)
+    if nl is not None:
+        s.set_nonlocal(nl)
+    E = [0.35, 1.3]
+    for side in (0, 1):
+        out = s.solve(E, opts=iobm.default_opts(precision=precision, side=side), want_psi=True)
+        assert out["status"] == 0, out.get("error")
+        psi = out["psi"].cpu().numpy().reshape(len(out["T"]), -1)
+        k = 0
+        for e, Ee in enumerate(E):
+            for m in out["modes"][e]:
+                b = P.rhs(Ee, int(m), "LR"[side]).ravel()
+                r = np.linalg.norm(P.apply(Ee, psi[k]).ravel() - b) / np.linalg.norm(b)
+                assert r <= 1e-9, (Ee, int(m), side, r)
+                k += 1
+        assert np.abs(out["T"] + out["R"] - 1).max() <= 1e-7
