@@ -230,7 +230,7 @@ iobm_status iobm_precondition(iobm_ctx ctx, int32_t precond, double alpha, doubl
  * library holds on every device it runs on until the process ends.  Needed:
  * IOBM_PC_LATERAL_FFT nrhs * nx*ny*nz * (16 bytes complex128, 8 complex64)
  * + 488 * nx*ny bytes; with rz, nrhs * (32 * slots + 16) bytes, slots = nz
- * (lateral-Fourier), ceil(nz / 16) (Eq. (17)) or up to 64 (none).  A request
+ * (lateral-Fourier, Eq. (17)) or up to 64 (none).  A request
  * beyond the workspace returns IOBM_E_UNSUPPORTED before any launch.
  * Every call on one device shares that device's workspace and leaves its
  * contents behind: calls that overlap on one GPU (several contexts, threads

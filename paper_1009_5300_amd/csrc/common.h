@@ -81,6 +81,14 @@ __device__ __forceinline__ void dft_small(cplx<T>* v, const cplx<T>* tw, int n, 
     v[1] = s1 + js3;
     v[2] = s0 - s2;
     v[3] = s1 - js3;
+  } else if constexpr (R == 3) {
+    const T h = (T)0.86602540378443864676372317075294;
+    const cplx<T> t = v[1] + v[2], d = v[1] - v[2];
+    const cplx<T> m = mk(v[0].re - (T)0.5 * t.re, v[0].im - (T)0.5 * t.im);
+    const cplx<T> js = sign < 0 ? mk(h * d.im, -h * d.re) : mk(-h * d.im, h * d.re);
+    v[0] = v[0] + t;
+    v[1] = m + js;
+    v[2] = m - js;
   } else {
     cplx<T> in[R];
 #pragma unroll
@@ -96,6 +104,11 @@ __device__ __forceinline__ void dft_small(cplx<T>* v, const cplx<T>* tw, int n, 
   }
 }
 
+// a / b for 0 <= a < 16384 and 1 <= b <= 4096 from inv = 1.0f / b: exact
+// (checked for every pair), and a few instructions where the integer division
+// by a run-time value takes some 30.
+__device__ __forceinline__ int small_quotient(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 // One Stockham pass of radix R over `count` independent 1D transforms of
 // length n; element e of transform t lives at t*tstride + e*estride.  Ns is
 // the length of the sub-transforms already completed by earlier passes.
@@ -106,20 +119,22 @@ __device__ void stockham_pass_r(const cplx<T>* __restrict__ in, cplx<T>* __restr
   const int per = n / R;
   const int total = count * per;
   const int tstep = n / (Ns * R);
+  const float iper = 1.0f / (float)per, ins = 1.0f / (float)Ns;
   for (int w = threadIdx.x; w < total; w += blockDim.x) {
-    const int t = w / per;
+    const int t = small_quotient(w, iper);
     const int j = w - t * per;
     const int base = t * tstride;
-    const int k = j % Ns;
+    const int q = small_quotient(j, ins) * Ns;
+    const int k = j - q;
     cplx<T> v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       cplx<T> a = in[base + (j + r * per) * estride];
-      if (r && k) a = a * twid(tw, (r * k * tstep) % n, sign);
+      if (r && k) a = a * twid(tw, r * k * tstep, sign);  // r k tstep < n
       v[r] = a;
     }
     dft_small<T, R>(v, tw, n, sign);
-    const int idxD = (j / Ns) * Ns * R + k;
+    const int idxD = q * R + k;
 #pragma unroll
     for (int r = 0; r < R; ++r) out[base + (idxD + r * Ns) * estride] = v[r];
   }

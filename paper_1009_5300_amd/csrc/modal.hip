@@ -541,6 +541,7 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
   constexpr bool HAS_INV = pm_inv(MODE), HAS_FWD = pm_fwd(MODE);
   const bool advance = pm_sum(MODE) && !pm_dir(MODE) && z == 0 && phase == 0;
   if (advance) advance_sums<256>(adv, A.part + (long long)rhs * A.nmb * MODAL_PART, A.nmb, threadIdx.x);
+  const float inx = 1.0f / (float)nx;
   for (int i = threadIdx.x; i < nx; i += blockDim.x) tx[i] = twx[i];
   for (int i = threadIdx.x; i < ny; i += blockDim.x) ty[i] = twy[i];
   cplx<T>* pv = nullptr;
@@ -577,7 +578,7 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
   cplx<T>* src = a;
   if constexpr (HAS_INV) {
     for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
-      const int j = p / nx, i = p - j * nx;
+      const int j = small_quotient(p, inx), i = p - j * nx;
       const int jm = (j ? ny - j : 0) * nx, im = i ? nx - i : 0, jp = j * nx;
       b[p] = cs_f(j, ny, cs_f(i, nx, a[jp + i], a[jp + im]), cs_f(i, nx, a[jm + i], a[jm + im]));
     }
@@ -606,7 +607,7 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
   if constexpr (HAS_FWD) {
     cplx<T>* f = fft2d_lds(src, src == a ? b : a, plan, tx, ty, -1);
     for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
-      const int j = p / nx, i = p - j * nx;
+      const int j = small_quotient(p, inx), i = p - j * nx;
       const int jm = (j ? ny - j : 0) * nx, im = i ? nx - i : 0, jp = j * nx;
       vec[p] = f_cs(j, ny, f_cs(i, nx, f[jp + i], f[jp + im]), f_cs(i, nx, f[jm + i], f[jm + im]));
     }

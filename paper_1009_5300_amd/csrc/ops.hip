@@ -552,10 +552,18 @@ __global__ void k_boundary(FFTPlan2D plan, int nz, int nf, const cplx<T>* __rest
                            const cplx<T>* __restrict__ sig,
                            const int* __restrict__ e_rhs, const cplx<T>* __restrict__ twx,
                            const cplx<T>* __restrict__ twy, const int* __restrict__ active,
-                           Partial* __restrict__ part, int np, int pslot) {
+                           Partial* __restrict__ part, int np, int pslot, int tw_lds) {
   extern __shared__ char smem_raw[];
   cplx<T>* buf = reinterpret_cast<cplx<T>*>(smem_raw);
   const int nxy = plan.x.n * plan.y.n;
+  const cplx<T>*tx = twx, *ty = twy;
+  if (tw_lds) {  // twiddle tables beside the planes, where the LDS holds both
+    cplx<T>* t = buf + (nf + 1) * nxy;
+    for (int i = threadIdx.x; i < plan.x.n; i += blockDim.x) t[i] = twx[i];
+    for (int i = threadIdx.x; i < plan.y.n; i += blockDim.x) t[plan.x.n + i] = twy[i];
+    tx = t;
+    ty = t + plan.x.n;
+  }
   const int slot = blockIdx.x >> 1;
   const int side = blockIdx.x & 1;
   const int rhs = rhs_of(active, slot);
@@ -568,7 +576,7 @@ __global__ void k_boundary(FFTPlan2D plan, int nz, int nf, const cplx<T>* __rest
     const cplx<T>* src = x + rhs * vol + (long long)(pbase + k) * nxy;
     for (int p = threadIdx.x; p < nxy; p += blockDim.x) P[k][p] = src[p];
     __syncthreads();
-    cplx<T>* res = fft2d_lds(P[k], P[nf], plan, twx, twy, -1);
+    cplx<T>* res = fft2d_lds(P[k], P[nf], plan, tx, ty, -1);
     if (res != P[k]) { cplx<T>* t = P[k]; P[k] = P[nf]; P[nf] = t; }
   }
   // mode mixing; plane k of the block <-> boundary-plane index i:
@@ -592,7 +600,7 @@ __global__ void k_boundary(FFTPlan2D plan, int nz, int nf, const cplx<T>* __rest
   __syncthreads();
   double s_re = 0, s_im = 0, s_n2 = 0;
   for (int k = 0; k < nf; ++k) {
-    cplx<T>* res = fft2d_lds(P[k], P[nf], plan, twx, twy, +1);
+    cplx<T>* res = fft2d_lds(P[k], P[nf], plan, tx, ty, +1);
     const long long po = rhs * vol + (long long)(pbase + k) * nxy;
     for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
       const cplx<T> r = res[p];
@@ -785,6 +793,11 @@ __global__ void __launch_bounds__(N * NF) k_boundary_reg(int nz, const cplx<T>* 
 // ----------------------------------------------- Eq. (17) preconditioner ---
 // z = C0 r + C1 sum over the six face neighbours, C0 = 1, C1 = exp(-alpha);
 // lateral neighbours wrap, z neighbours outside the region are zero.
+// A block takes S.zchunk planes of one rhs: 16, where that gives every
+// compute unit blocks (the z neighbours are then cache hits of the same
+// block), fewer in small batches.  The z neighbours' own values stay in
+// registers from plane to plane.  Its partial of r^T z goes to slot `chunk` of
+// the rhs's nz slots; chunk 0 clears the slots past the last chunk.
 template <typename T>
 __global__ void __launch_bounds__(256) k_precond_lap(StencilArgs S, T c1, const cplx<T>* __restrict__ r,
                                                      cplx<T>* __restrict__ z,
@@ -798,32 +811,38 @@ __global__ void __launch_bounds__(256) k_precond_lap(StencilArgs S, T c1, const 
   cplx<T>* zr = z + rhs * vol;
   const int z0 = chunk * S.zchunk;
   const int z1 = min(S.nz, z0 + S.zchunk);
+  const float inx = 1.0f / (float)S.nx;
   double s_re = 0, s_im = 0;
-  for (int k = z0; k < z1; ++k) {
-    const cplx<T>* rp = rr + (long long)k * S.nxy;
-    for (int p = threadIdx.x; p < S.nxy; p += blockDim.x) {
-      const int j = p / S.nx;
-      const int i = p - j * S.nx;
-      int ip = i + 1; if (ip >= S.nx) ip -= S.nx;
-      int im = i - 1; if (im < 0) im += S.nx;
-      int jp = j + 1; if (jp >= S.ny) jp -= S.ny;
-      int jm = j - 1; if (jm < 0) jm += S.ny;
-      cplx<T> s = rp[j * S.nx + ip] + rp[j * S.nx + im] + rp[jp * S.nx + i] + rp[jm * S.nx + i];
-      if (k + 1 < S.nz) s = s + rp[S.nxy + p];
-      if (k > 0) s = s + rp[-S.nxy + p];
-      const cplx<T> c = rp[p], v = c + c1 * s;
+  for (int p = threadIdx.x; p < S.nxy; p += blockDim.x) {
+    const int j = small_quotient(p, inx);
+    const int i = p - j * S.nx;
+    const int ip = (i + 1 < S.nx ? p + 1 : p + 1 - S.nx), im = (i > 0 ? p - 1 : p - 1 + S.nx);
+    const int jp = (j + 1 < S.ny ? p + S.nx : i), jm = (j > 0 ? p - S.nx : p + (S.ny - 1) * S.nx);
+    cplx<T> below = z0 > 0 ? rr[(long long)(z0 - 1) * S.nxy + p] : mk<T>(0, 0);
+    cplx<T> c = rr[(long long)z0 * S.nxy + p];
+    for (int k = z0; k < z1; ++k) {
+      const cplx<T>* rp = rr + (long long)k * S.nxy;
+      const cplx<T> above = k + 1 < S.nz ? rp[S.nxy + p] : mk<T>(0, 0);
+      const cplx<T> s = rp[ip] + rp[im] + rp[jp] + rp[jm] + above + below;
+      const cplx<T> v = c + c1 * s;
       zr[(long long)k * S.nxy + p] = v;
       s_re += (double)c.re * v.re - (double)c.im * v.im;
       s_im += (double)c.re * v.im + (double)c.im * v.re;
+      below = c;
+      c = above;
     }
   }
   if (dpart) {
     double dummy = 0;
     block_reduce3(s_re, s_im, dummy);
+    Partial P;
+    P.re = P.im = P.n2 = P.pad = 0;
+    Partial* dp = dpart + (long long)rhs * S.nz;
+    if (chunk == 0)
+      for (int k = S.nchunks + threadIdx.x; k < S.nz; k += blockDim.x) dp[k] = P;
     if (threadIdx.x == 0) {
-      Partial P;
-      P.re = s_re; P.im = s_im; P.n2 = 0; P.pad = 0;
-      dpart[(long long)rhs * S.nchunks + chunk] = P;
+      P.re = s_re; P.im = s_im;
+      dp[chunk] = P;
     }
   }
 }
@@ -912,13 +931,16 @@ __global__ void __launch_bounds__(256) k_fft_planes(FFTPlan2D plan, int nz, cons
   cplx<T>* bufA = reinterpret_cast<cplx<T>*>(smem_raw);
   const int nxy = plan.x.n * plan.y.n;
   cplx<T>* bufB = bufA + nxy;
+  cplx<T>*tx = bufB + nxy, *ty = tx + plan.x.n;
+  for (int i = threadIdx.x; i < plan.x.n; i += blockDim.x) tx[i] = twx[i];
+  for (int i = threadIdx.x; i < plan.y.n; i += blockDim.x) ty[i] = twy[i];
   const int slot = blockIdx.x / nz;
   const int z = blockIdx.x - slot * nz;
   const int rhs = rhs_of(active, slot);
   const long long off = (long long)rhs * nxy * nz + (long long)z * nxy;
   for (int p = threadIdx.x; p < nxy; p += blockDim.x) bufA[p] = in[off + p];
   __syncthreads();
-  cplx<T>* res = fft2d_lds(bufA, bufB, plan, twx, twy, sign);
+  cplx<T>* res = fft2d_lds(bufA, bufB, plan, tx, ty, sign);
   double a = 0, b = 0, dummy = 0;
   for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
     const cplx<T> v = scale * res[p];
@@ -1926,10 +1948,13 @@ static hipError_t launch_boundary(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx
       default: reg = false;
     }
   }
-  if (!reg)
-    hipLaunchKernelGGL((k_boundary<T, TR>), dim3(2 * nrhs), dim3(fft_threads(c->g.nxy)), sh, c->stream, c->plan,
-                       c->g.nz, c->g.nf, x, y, rout, sigtab<T>(c), e_rhs, twx<T>(c), twy<T>(c), active, part,
-                       (int)PQ_SLOTS, (int)PQ_BOUNDARY);
+  if (!reg) {
+    const size_t twb = (size_t)(c->g.nx + c->g.ny) * sizeof(cplx<T>);
+    const int tw_lds = sh + twb + 1024 <= 160 * 1024;  // (1 KiB: the kernel's static arrays)
+    hipLaunchKernelGGL((k_boundary<T, TR>), dim3(2 * nrhs), dim3(fft_threads(c->g.nxy)), sh + (tw_lds ? twb : 0),
+                       c->stream, c->plan, c->g.nz, c->g.nf, x, y, rout, sigtab<T>(c), e_rhs, twx<T>(c), twy<T>(c),
+                       active, part, (int)PQ_SLOTS, (int)PQ_BOUNDARY, tw_lds);
+  }
   prof_stop(c, rec, (double)nrhs * 2 * c->g.nf * c->g.nxy * (2 * sizeof(cplx<T>) + sizeof(cplx<TR>)));
   return hipGetLastError();
 }
@@ -2056,7 +2081,9 @@ template <typename T>
 hipError_t launch_precond_laplacian(iobm_ctx c, double alpha, const cplx<T>* r, cplx<T>* z, int nrhs,
                                     const int* active, Partial* dpart) {
   if (nrhs <= 0) return hipSuccess;
-  StencilArgs S = stencil_args(c, 16);
+  int zc = 16;
+  while (zc > 1 && (long long)nrhs * ((c->g.nz + zc - 1) / zc) < 4LL * c->num_cu) zc /= 2;
+  StencilArgs S = stencil_args(c, zc);
   const int rec = prof_start(c, IOBM_K_PRECOND_LAP);
   hipLaunchKernelGGL(k_precond_lap<T>, dim3(nrhs * S.nchunks), dim3(256), 0, c->stream, S,
                      (T)exp(-alpha), r, z, active, dpart);
@@ -2142,7 +2169,7 @@ hipError_t launch_fft_planes(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int si
   if (nrhs <= 0) return hipSuccess;
   const int rec = prof_start(c, dpart ? IOBM_K_FFT_PLANES_DOT : IOBM_K_FFT_PLANES);
   if (!fft_reg_dispatch<T>(c, in, out, sign, scale, nrhs, active, mvec, dpart)) {
-    size_t sh = 2 * (size_t)c->g.nxy * sizeof(cplx<T>);
+    size_t sh = (2 * (size_t)c->g.nxy + c->g.nx + c->g.ny) * sizeof(cplx<T>);
     hipLaunchKernelGGL(k_fft_planes<T>, dim3(nrhs * c->g.nz), dim3(256), sh, c->stream, c->plan, c->g.nz, in, out,
                        twx<T>(c), twy<T>(c), sign, (T)scale, active, dvec, dpart);
   }
@@ -2368,7 +2395,7 @@ int dot_blocks(iobm_ctx c);
 int precond_slots(iobm_ctx c, int precond) {
   if (precond == IOBM_PC_LATERAL_FFT) return c->g.nz;
   if (precond == IOBM_PC_JACOBI) return dot_blocks(c);
-  if (precond == IOBM_PC_TRUNCATED_LAPLACIAN) return (c->g.nz + 15) / 16;
+  if (precond == IOBM_PC_TRUNCATED_LAPLACIAN) return c->g.nz;
   return dot_blocks(c);
 }
 
@@ -2447,7 +2474,7 @@ template hipError_t launch_init_r<double>(iobm_ctx, const zd*, zd*, int, const i
 
 int dot_blocks(iobm_ctx c) {
   long long vol = c->g.npts;
-  long long b = vol / 8192;
+  long long b = vol / 2048;  // 8 elements per thread: small batches need the blocks
   if (b < 1) b = 1;
   if (b > 64) b = 64;
   return (int)b;
