@@ -417,7 +417,7 @@ enum { IOBM_K_STENCIL = 1,      /* stencil in the iteration precision; with the
        IOBM_K_NONLOCAL_C128 = 12, /* as IOBM_K_NONLOCAL, complex128 (flops) */
        IOBM_K_FFT_PLANES_DOT = 13, /* inverse plane FFT with the r^T z partials */
        IOBM_K_FFT_PLANES_UPD = 14, /* plane pass of the mode-space iteration, Z -> V z -> W
-                                   (2 streams; 4 with a stored direction) */
+                                   (2 streams) */
        IOBM_K_PRECOND_JACOBI = 15,  /* Jacobi preconditioner: read r, write z */
        IOBM_K_BLOCK_GRAM = 16,      /* block COCG: s x s Grams of a group (MFMA f64) + their
                                        fixed-order sum; bytes: read both blocks once */

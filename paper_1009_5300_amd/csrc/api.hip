@@ -507,7 +507,7 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
     if (modal) {
       double reads = 0;  // vectors of the ring (and its fold) that make up the correction
       for (int i : lst)
-        reads += since[i] >= modal_short_steps<T>() ? 1 : (since[i] < kRing - 1 ? since[i] : since[i] % (kRing - 1) + 2);
+        reads += since[i] < kRing - 1 ? since[i] : since[i] % (kRing - 1) + 2;
       HIPCHK(modal_correct<T>(ctx, MD, x, xset, n, ld, reads, nfirst));
     } else {
       HIPCHK(launch_accumulate<T>(ctx, x, d, pold, alpha, xset, dlive, n, ld, nfirst, ndead));
@@ -580,17 +580,9 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   auto enqueue_check = [&]() {
     if (modal) {
       for (int k = 0; k < check; ++k) {
-        constexpr int kShort = modal_short_steps<T>();
-        ModalPlan plan;
-        for (int i : act) {
-          const int n = since[i] + k;  // steps before this one
-          plan.fastp = plan.fastp || n < kShort;
-          plan.slowp = plan.slowp || n >= kShort;
-          plan.fold = plan.fold || (n < kShort && (n + 1) % (kRing - 1) == 0);
-          plan.turn = plan.turn || n + 1 == kShort;
-        }
-        if (graphs) plan.fastp = plan.slowp = plan.fold = plan.turn = true;  // a captured sequence covers any count
-        HIPCHK(modal_step<T>(ctx, MD, nact, act_d, plan));
+        bool fold = graphs;  // a captured sequence covers any count
+        for (int i : act) fold = fold || (since[i] + k + 1) % (kRing - 1) == 0;
+        HIPCHK(modal_step<T>(ctx, MD, nact, act_d, fold));
       }
       HIPCHK(modal_check<T>(ctx, MD, nact, act_d, rn2, flag));
       return;

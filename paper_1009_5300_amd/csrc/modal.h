@@ -9,15 +9,10 @@ template <typename T> struct ModalRing;
 template <> struct ModalRing<float> { static constexpr int n = 6; };
 template <> struct ModalRing<double> { static constexpr int n = 5; };
 
-// Steps after a replacement that take the short recurrence; a right-hand
-// side that is still iterating then goes over to the stored direction (a
-// multiple of n - 1, when the ring has just been folded).
-template <typename T> constexpr int modal_short_steps() { return 4 * (ModalRing<T>::n - 1); }
-
 // Planes per chunk of the mode pass (a power of two).
 constexpr int kModalChunk = 8;
 
-enum { MODAL_PART = 7 };  // values per block partial of the mode pass: rho, sigma, |r|^2, tau
+enum { MODAL_PART = 5 };  // values per block partial of the mode pass: rho, sigma, |r|^2
 
 // Scalars of one right-hand side.  The plane pass of a step advances them
 // from the last mode pass's partials; the mode pass reads them.
@@ -25,13 +20,10 @@ struct ModalScal {
   zd rho, sigma;          // r^T z and z^T q_old of the current residual
   zd rho_old, alpha_old;  // of the last step
   zd alpha;               // written by the mode pass of the step
-  zd beta, tau;           // stored direction: beta and s^T p of the step
   double n2;              // |r|^2
   int step;               // index of the current residual since the last replacement
   int base;               // residuals before this one are folded into S and T
   int flag;               // breakdown
-  int phase;              // 0 short recurrence; 1, 2 stored direction (its first step, later)
-  int rslot;              // stored direction: ring slot of the residual (p in the next one)
   int pad_;
 };
 
@@ -58,7 +50,6 @@ struct PlaneArgs {
   double* dpart;
   zd* x = nullptr;
   const int* xset = nullptr;
-  cplx<T>* ring[ModalRing<T>::n];
   KBPlane<T> kb;
 };
 
@@ -103,16 +94,10 @@ hipError_t modal_setup(iobm_ctx c, Modal<T>& M);
 // (re)start the listed rhs from the real-space residual in ring slot 0
 template <typename T>
 hipError_t modal_start(iobm_ctx c, const Modal<T>& M, int nact, const int* active);
-// one iteration of the listed rhs.  What it has to launch follows from the
-// steps each has taken since its replacement: fastp / slowp, any takes the
-// short recurrence / the stored direction; fold, a ring is full after this
-// step; turn, a rhs goes over to the stored direction after it.  (More than
-// needed is harmless: every kernel checks its right-hand side.)
-struct ModalPlan {
-  bool fastp = false, slowp = false, fold = false, turn = false;
-};
+// one iteration of the listed rhs; fold: the ring of some may be full after it
+// (the kernels check which, so that true is always right)
 template <typename T>
-hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active, const ModalPlan& plan);
+hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active, bool fold);
 // x += d (x written without being read where xset = 0); ring_reads and nfirst
 // are for the timing hook's byte count
 template <typename T>

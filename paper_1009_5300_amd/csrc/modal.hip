@@ -13,23 +13,23 @@
 //                  q  = (R - W) + (beta / alpha_old) (R_old - R),
 //                  R' = R - alpha q,   Z = P R' (recursive z filter),
 //                partials of rho' = r'^T z, sigma' = z^T q and |r'|^2
-// with beta = rho / rho_old and alpha = rho / mu,
-//   mu = p^T A p = z^T q = rho - z^T W + beta z^T q_old   (p_old^T A p = 0).
+// with
+//   beta  = -sigma alpha_old / rho_old   (z^T A p_old + beta p_old^T A p_old = 0),
+//   alpha = rho / mu,  mu = p^T A p = z^T q = rho - z^T W + beta sigma.
 // The solution correction of n steps is d = P t, t = sum_j alpha_j s_j with
 // s_j = r_j + beta_j s_(j-1), a combination of the residuals r_0 .. r_(n-1):
-// they are kept in a ring of vectors, and d is formed once, when the residual
-// is replaced.  An iteration moves 7 vector streams (plane pass 2, mode pass 5).
+// they are kept in a ring of vectors, folded into S and T when it is full,
+// and d is formed once, when the residual is replaced.  An iteration moves 7
+// vector streams (plane pass 2, mode pass 5).
 //
-// The rounding of q, carried from step to step, grows on systems that need
-// hundreds of steps (a NumPy model of the Na-like wire did not converge in
-// complex64).  A right-hand side still iterating after modal_short_steps()
-// therefore goes over to the stored direction: s (= A0 p) and p are kept,
-//   plane pass   p = z + beta p_old,  U = V p,  partials of p^T U;
-//   mode pass    s = r + beta s_old,  q = s - U,  R' = R - alpha q,  t += alpha s,
-//                Z = P R',  partials of rho', sigma' = z^T s and |r'|^2,
-//   mu = tau - p^T U,  tau = s^T p = rho + 2 beta sigma + beta^2 tau_old,
-// 12 streams; q is formed from p itself, as A p would be (in that model 1225
-// to 1279 iterations against 1466 of the recurrence with A p).
+// Why this beta and not rho / rho_old (the same number in exact arithmetic):
+// it makes the new direction conjugate to the last one as computed, so the
+// rounding that R_old - R brings into q is corrected from step to step instead
+// of being carried along.  With rho / rho_old 5 of 5,664 solves of a 24 x 24 x 96
+// chain with projectors took 500 to 2,700 iterations and a Na-like wire did not
+// converge in complex64; with this one the most in 14,160 solves of the chain is
+// 319 (mean 108.1; the recurrence with A p: 255 in 3,776, mean 109.9), and the
+// wire takes 2,219 against 2,166.
 //
 // Real lateral basis.  Complex vectors are transformed with the real
 // cos/sin pairs of the discrete Fourier transform along each lateral
@@ -77,23 +77,12 @@ template <> struct Vec16<double> {
 //   PM_VFWD  z -> W in place (the second half: V z plus the nonlocal term);
 //   PM_FWD   r -> R in place (a replaced residual);
 //   PM_ACC   x += inverse transform of D (x not read where xset = 0).
-//   PM_DFULL, PM_DINV  PM_FULL and PM_INV of the stored direction: the input
-//            is p = Z + beta p_old, written to p's ring slot.
-// PM_FULL, PM_DFULL and PM_VFWD write the plane's partial of z^T V z (p^T V p)
-// and, on plane 0 of a right-hand side with the short recurrence, advance its
-// scalars by one step.
-enum { PM_FULL = 0, PM_INV = 1, PM_VFWD = 2, PM_FWD = 3, PM_ACC = 4, PM_DFULL = 5, PM_DINV = 6 };
-constexpr bool pm_dir(int mode) { return mode == PM_DFULL || mode == PM_DINV; }
-constexpr bool pm_pot(int mode) { return mode == PM_FULL || mode == PM_DFULL; }  // V between the two transforms
-constexpr bool pm_inv(int mode) { return pm_pot(mode) || mode == PM_INV || mode == PM_DINV || mode == PM_ACC; }
-constexpr bool pm_fwd(int mode) { return pm_pot(mode) || mode == PM_VFWD || mode == PM_FWD; }
-constexpr bool pm_sum(int mode) { return pm_pot(mode) || mode == PM_VFWD; }
-// whether the pass covers this right-hand side in its phase
-__device__ __forceinline__ bool pm_covers(int mode, int phase) {
-  if (mode == PM_FULL || mode == PM_INV) return phase == 0;
-  if (pm_dir(mode)) return phase != 0;
-  return true;
-}
+// PM_FULL and PM_VFWD write the plane's partial of z^T V z and, on plane 0 of
+// a right-hand side, advance its scalars by one step.
+enum { PM_FULL = 0, PM_INV = 1, PM_VFWD = 2, PM_FWD = 3, PM_ACC = 4 };
+constexpr bool pm_inv(int mode) { return mode == PM_FULL || mode == PM_INV || mode == PM_ACC; }
+constexpr bool pm_fwd(int mode) { return mode == PM_FULL || mode == PM_VFWD || mode == PM_FWD; }
+constexpr bool pm_sum(int mode) { return mode == PM_FULL || mode == PM_VFWD; }
 
 // Scalars of the step that begins: the sums of the mode pass's block partials
 // (fixed order), and the last step's rho and alpha moved to *_old.  A group
@@ -307,18 +296,12 @@ __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__(
   __shared__ cplx<T> sm[PPB][N][N + 1];
   const int pl = threadIdx.x / TP, lt = threadIdx.x - pl * TP;
   const int gp = blockIdx.x * PPB + pl;
-  // a group past the last plane repeats it and stores nothing (nor does a
-  // group whose right-hand side is in the other phase), so that no load sits
-  // under a branch
+  // a group past the last plane repeats it and stores nothing, so that no load
+  // sits under a branch
   const int gq = min(gp, A.nplanes - 1);
   const int slot = gq / A.nz, z = gq - slot * A.nz;
   const int rhs = rhs_of(A.active, slot);
-  const bool ok = gp < A.nplanes && pm_covers(MODE, A.sc[rhs].phase);
-  if constexpr (PPB == 1) {
-    if (!ok) return;
-  } else {
-    if (!__syncthreads_or(ok)) return;
-  }
+  const bool ok = gp < A.nplanes;
   const long long off = ((long long)rhs * A.nz + z) * NN;
   cplx<T>* vec = A.vec + off;
   const int li = lt / SPLIT, half = lt % SPLIT;
@@ -326,8 +309,8 @@ __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__(
   constexpr bool HAS_INV = pm_inv(MODE), HAS_FWD = pm_fwd(MODE);
   const T scale = (T)(0.25 / NN);
   double d_re = 0, d_im = 0;
-  __shared__ double adv[pm_sum(MODE) && !pm_dir(MODE) ? PPB : 1][adv_subs(TP) * kAdvValues];
-  const bool advance = pm_sum(MODE) && !pm_dir(MODE) && ok && z == 0 && A.sc[rhs].phase == 0;
+  __shared__ double adv[pm_sum(MODE) ? PPB : 1][adv_subs(TP) * kAdvValues];
+  const bool advance = pm_sum(MODE) && ok && z == 0;
   if (advance) advance_sums<TP>(adv[pl], A.part + (long long)rhs * A.nmb * MODAL_PART, A.nmb, lt);
   // stage the plane in LDS, all of a thread's loads in flight together
   {
@@ -351,22 +334,6 @@ __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__(
           sm[pl][e * ROWS + r0][c0 + k] = u;
         }
       asm volatile("" : "+v"(d_re), "+v"(d_im));  // the sums are taken here (see the inverse path)
-    } else if constexpr (pm_dir(MODE)) {
-      const cplx<T> beta = cvt<T>(A.sc[rhs].beta);
-      VT* pv = reinterpret_cast<VT*>(ring_at<T>(A.ring, (A.sc[rhs].rslot + 1) % ModalRing<T>::n) + off);
-      VT pb[EPT];
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) pb[e] = pv[lt + e * TP];
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-#pragma unroll
-        for (int k = 0; k < PE; ++k) {
-          const cplx<T> p = cfma(beta, Vec16<T>::get(pb[e], k), Vec16<T>::get(buf[e], k));
-          Vec16<T>::set(pb[e], k, p);
-          sm[pl][e * ROWS + r0][c0 + k] = p;
-        }
-        if (ok) pv[lt + e * TP] = pb[e];
-      }
     } else {
 #pragma unroll
       for (int e = 0; e < EPT; ++e)
@@ -398,7 +365,7 @@ __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__(
     for (int i = 0; i < M; ++i) sm[pl][li][i + half * M] = v[i];
     __syncthreads();
     inverse_line<T, N, SPLIT>(&sm[pl][0][li], N + 1, half, v);  // column li
-    if constexpr (pm_pot(MODE)) {
+    if constexpr (MODE == PM_FULL) {
       // V of this column in batches: all of it in flight during the transform
       // would not fit the registers (N = 48: 380 B of scratch per lane)
       const T* V = potential<T>(A.Vd, A.Vf) + (long long)z * NN + li;
@@ -532,30 +499,18 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
   double* adv = red + 8;                             // [16][5]
   const int slot = blockIdx.x / A.nz, z = blockIdx.x - slot * A.nz;
   const int rhs = rhs_of(A.active, slot);
-  const int phase = A.sc[rhs].phase;
-  if (!pm_covers(MODE, phase)) return;
   const long long off = ((long long)rhs * A.nz + z) * nxy;
   cplx<T>* vec = A.vec + off;
   const T* V = potential<T>(A.Vd, A.Vf) + (long long)z * nxy;
   double d_re = 0, d_im = 0;
   constexpr bool HAS_INV = pm_inv(MODE), HAS_FWD = pm_fwd(MODE);
-  const bool advance = pm_sum(MODE) && !pm_dir(MODE) && z == 0 && phase == 0;
+  const bool advance = pm_sum(MODE) && z == 0;
   if (advance) advance_sums<256>(adv, A.part + (long long)rhs * A.nmb * MODAL_PART, A.nmb, threadIdx.x);
   const float inx = 1.0f / (float)nx;
   for (int i = threadIdx.x; i < nx; i += blockDim.x) tx[i] = twx[i];
   for (int i = threadIdx.x; i < ny; i += blockDim.x) ty[i] = twy[i];
-  cplx<T>* pv = nullptr;
-  cplx<T> beta = mk<T>(0, 0);
-  if constexpr (pm_dir(MODE)) {
-    pv = ring_at<T>(A.ring, (A.sc[rhs].rslot + 1) % ModalRing<T>::n) + off;
-    beta = cvt<T>(A.sc[rhs].beta);
-  }
   for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
     cplx<T> c = vec[p];
-    if constexpr (pm_dir(MODE)) {
-      c = cfma(beta, pv[p], c);
-      pv[p] = c;
-    }
     if constexpr (MODE == PM_VFWD) {
       const cplx<T> u = V[p] * c;
       d_re += (double)c.re * u.re - (double)c.im * u.im;
@@ -592,7 +547,7 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
         const zd d = cvt<double>(scale * src[p]);
         x[p] = have ? x[p] + d : d;
       }
-    } else if constexpr (!pm_pot(MODE)) {
+    } else if constexpr (MODE != PM_FULL) {
       for (int p = threadIdx.x; p < nxy; p += blockDim.x) vec[p] = scale * src[p];
     } else {
       for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
@@ -634,11 +589,8 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
 // -------------------------------------------------------------- mode pass ---
 // ZS_STEP   one iteration's update and preconditioner (see the top of the file);
 // ZS_START  Z = P R of a replaced residual (ring slot 0), the step count reset;
-// ZS_FOLD   D = P t, the correction of the steps since the last replacement;
-// ZS_TURN   p = P s of the direction just folded (the right-hand sides that go
-//           over to the stored direction), partials of z^T s and s^T p;
-// ZS_DSTEP  the update and preconditioner with the stored direction.
-enum { ZS_STEP = 0, ZS_START = 1, ZS_FOLD = 2, ZS_TURN = 3, ZS_DSTEP = 4 };
+// ZS_FOLD   D = P t, the correction of the steps since the last replacement.
+enum { ZS_STEP = 0, ZS_START = 1, ZS_FOLD = 2 };
 
 // a / b, and whether b is nonzero and the quotient finite
 __device__ __forceinline__ bool quotient(zd a, zd b, zd& r) {
@@ -738,25 +690,19 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
     }
   };
   ModalScal& S = A.sc[rhs];
-  const int phase = __builtin_amdgcn_readfirstlane(S.phase), step = __builtin_amdgcn_readfirstlane(S.step);
-  const int rslot = __builtin_amdgcn_readfirstlane(S.rslot);
-  if ((MODE == ZS_STEP && phase != 0) || (MODE == ZS_DSTEP && phase == 0) ||
-      (MODE == ZS_TURN && (phase != 0 || step + 1 != modal_short_steps<T>())))
-    return;  // the whole block
-  constexpr bool STEP = MODE == ZS_STEP || MODE == ZS_DSTEP;
+  const int step = __builtin_amdgcn_readfirstlane(S.step);
+  constexpr bool STEP = MODE == ZS_STEP;
   // own inputs; rr[NF - 1 + i] is plane z0 + i
   cplx<T> rr[L + 2 * NF - 1];
-  cplx<T> q[STEP ? L : 1];  // the vector of sigma' = z^T q (z^T s)
+  cplx<T> q[STEP ? L : 1];
   if constexpr (STEP) {
     const int k = step;
-    // the third input: the previous residual, or the direction s
-    const cplx<T>* X = MODE == ZS_DSTEP ? A.fold_s + rhs * A.fold_stride
-                                        : ring_at<T>(A.ring, k > 0 ? (k - 1) % NR : 0) + base;
+    const cplx<T>* X = ring_at<T>(A.ring, k > 0 ? (k - 1) % NR : 0) + base;
     cplx<T> xo[L];
-    load(ring_at<T>(A.ring, MODE == ZS_STEP ? k % NR : rslot) + base, rr + NF - 1);
+    load(ring_at<T>(A.ring, k % NR) + base, rr + NF - 1);
     load(A.w + base, q);
     load(X, xo);
-    // z^T W (p^T U) of this right-hand side, summed in a fixed order, and the
+    // z^T W of this right-hand side, summed in a fixed order, and the
     // step's scalars: by the first wavefront, while the loads are in flight
     __shared__ zd sco[2];
     if (c < 64 / MB) {
@@ -767,22 +713,15 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
       for (int o = 32; o > 0; o >>= 1) dl = dl + mk(__shfl_xor(dl.re, o), __shfl_xor(dl.im, o));
       zd beta = mk(0.0, 0.0), g = mk(0.0, 0.0), alpha;
       bool good = true;
-      if (MODE == ZS_DSTEP) {
-        beta = S.beta;
-        good = quotient(S.rho, S.tau - dl, alpha);
-      } else {
-        if (k > 0) good = quotient(S.rho, S.rho_old, beta) && quotient(beta, S.alpha_old, g);
-        good = quotient(S.rho, S.rho - dl + beta * S.sigma, alpha) && good;
-      }
+      if (k > 0) good = quotient(-(S.sigma * S.alpha_old), S.rho_old, beta) && quotient(-S.sigma, S.rho_old, g);
+      good = quotient(S.rho, S.rho - dl + beta * S.sigma, alpha) && good;
       if (wl == 0) {
         sco[0] = alpha;
-        sco[1] = MODE == ZS_STEP ? g : beta;
+        sco[1] = g;  // beta / alpha_old
         if (mb == 0) {
           S.alpha = alpha;
-          if (MODE == ZS_STEP) {
-            A.ha[(long long)rhs * NR + k % NR] = alpha;
-            A.hb[(long long)rhs * NR + k % NR] = beta;
-          }
+          A.ha[(long long)rhs * NR + k % NR] = alpha;
+          A.hb[(long long)rhs * NR + k % NR] = beta;
           if (!good) S.flag = 1;
         }
       }
@@ -795,33 +734,17 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const cplx<T> r = rr[NF - 1 + i];
-      cplx<T> qi;
-      if constexpr (MODE == ZS_STEP) {
-        qi = q[i] = cfma(ct, xo[i] - r, r - q[i]);
-      } else {
-        const cplx<T> s = cfma(ct, xo[i], r);
-        qi = s - q[i];
-        q[i] = s;
-      }
-      rr[NF - 1 + i] = cfma(-at_, qi, r);
+      q[i] = cfma(ct, xo[i] - r, r - q[i]);
+      rr[NF - 1 + i] = cfma(-at_, q[i], r);
     }
-    store(ring_at<T>(A.ring, MODE == ZS_STEP ? (k + 1) % NR : rslot) + base, rr + NF - 1);
-    if constexpr (MODE == ZS_DSTEP) {
-      cplx<T>* Tv = A.fold_t + rhs * A.fold_stride;
-      store(A.fold_s + rhs * A.fold_stride, q);
-      load(Tv, xo);
-#pragma unroll
-      for (int i = 0; i < L; ++i) xo[i] = cfma(at_, q[i], xo[i]);
-      store(Tv, xo);
-    }
-  } else if constexpr (MODE == ZS_START || MODE == ZS_TURN) {
-    load(MODE == ZS_START ? A.ring[0] + base : A.fold_s + rhs * A.fold_stride, rr + NF - 1);
+    store(ring_at<T>(A.ring, (k + 1) % NR) + base, rr + NF - 1);
+  } else if constexpr (MODE == ZS_START) {
+    load(A.ring[0] + base, rr + NF - 1);
     mask(rr + NF - 1);
-    if (MODE == ZS_START && mb == 0 && c == 0 && lane == 0) {
+    if (mb == 0 && c == 0 && lane == 0) {
       S.step = -1;  // the next plane pass makes it 0
       S.base = 0;
       S.flag = 0;
-      S.phase = 0;
       S.alpha = mk(0.0, 0.0);
     }
   } else {
@@ -834,15 +757,15 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
 #pragma unroll
       for (int i = 0; i < L; ++i) rr[NF - 1 + i] = cfma(f, t[i], rr[NF - 1 + i]);
     };
-    if (phase == 0) {
-      zd ct[NR], cs[NR], tp, sp;
-      ring_coeffs<NR>(A.ha + (long long)rhs * NR, A.hb + (long long)rhs * NR, b0, n, ct, cs, tp, sp);
+    zd ct[NR], cs[NR], tp, sp;
+    ring_coeffs<NR>(A.ha + (long long)rhs * NR, A.hb + (long long)rhs * NR, b0, n, ct, cs, tp, sp);
 #pragma unroll
-      for (int j = 0; j < NR; ++j)
-        if (b0 + j < n) add(ring_at<T>(A.ring, (b0 + j) % NR) + base, cvt<T>(ct[j]));
-      if (b0 > 0) add(A.fold_s + rhs * A.fold_stride, cvt<T>(tp));
+    for (int j = 0; j < NR; ++j)
+      if (b0 + j < n) add(ring_at<T>(A.ring, (b0 + j) % NR) + base, cvt<T>(ct[j]));
+    if (b0 > 0) {
+      add(A.fold_s + rhs * A.fold_stride, cvt<T>(tp));
+      add(A.fold_t + rhs * A.fold_stride, mk<T>(1, 0));
     }
-    if (b0 > 0) add(A.fold_t + rhs * A.fold_stride, mk<T>(1, 0));
     mask(rr + NF - 1);
   }
   // filter coefficients of this mode: [al | fb | fbb | M^L] (coalesced)
@@ -936,32 +859,20 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
 #pragma unroll
     for (int i = L - 1; i >= 0; --i) respond(h, y[i]);
   }
-  store((MODE == ZS_TURN ? ring_at<T>(A.ring, (step + 2) % NR) : A.w) + base, y);
+  store(A.w + base, y);
   if constexpr (MODE != ZS_FOLD) {
-    // bilinear products: rho' = r'^T z, sigma' = z^T q (z^T s), |r'|^2; the
-    // turn takes z^T s with the z of the last step and s^T p
+    // bilinear products: rho' = r'^T z, sigma' = z^T q, |r'|^2
     double d[5] = {0, 0, 0, 0, 0};
-    cplx<T> zo[MODE == ZS_TURN ? L : 1];
-    if constexpr (MODE == ZS_TURN) {
-      load(A.w + base, zo);
-      mask(zo);
-    }
     // (past the region r and q vanish, and with them every product)
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const cplx<T> r = rr[NF - 1 + i], zz = y[i];
       d[0] += (double)r.re * zz.re - (double)r.im * zz.im;
       d[1] += (double)r.re * zz.im + (double)r.im * zz.re;
-      if constexpr (STEP || MODE == ZS_TURN) {
-        cplx<T> u = zz, v;
-        if constexpr (MODE == ZS_TURN) {
-          u = zo[i];
-          v = r;
-        } else {
-          v = q[i];
-        }
-        d[2] += (double)v.re * u.re - (double)v.im * u.im;
-        d[3] += (double)v.re * u.im + (double)v.im * u.re;
+      if constexpr (STEP) {
+        const cplx<T> v = q[i];
+        d[2] += (double)v.re * zz.re - (double)v.im * zz.im;
+        d[3] += (double)v.re * zz.im + (double)v.im * zz.re;
       }
       d[4] += (double)r.re * r.re + (double)r.im * r.im;
     }
@@ -973,13 +884,11 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
     for (int k = 0; k < 5; ++k) red[(c * 5 + k) * MB + lane] = w * d[k];
     __syncthreads();
     // the threads of chunk c sum the values c, c + C, ...: chunks in order, then lanes
-    for (int k = c; k < (MODE == ZS_TURN ? 4 : 5); k += C) {
+    for (int k = c; k < 5; k += C) {
       double s = 0;
       for (int cc = 0; cc < C; ++cc) s += red[(cc * 5 + k) * MB + lane];
       for (int o = MB / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      // the turn's s^T p goes to the tau slots
-      const int to = MODE == ZS_TURN && k < 2 ? k + 5 : k;
-      if (lane == 0) A.part[((long long)rhs * A.nmb + mb) * MODAL_PART + to] = s;
+      if (lane == 0) A.part[((long long)rhs * A.nmb + mb) * MODAL_PART + k] = s;
     }
   }
 }
@@ -991,7 +900,7 @@ __global__ void __launch_bounds__(256) k_ring_fold(ModeArgsZ<T> A, long long vol
   constexpr int NR = ModalRing<T>::n;
   const int rhs = rhs_of(A.active, blockIdx.y);
   const int n = A.sc[rhs].step + 1, b0 = A.sc[rhs].base;
-  if (A.sc[rhs].phase != 0 || n - b0 != NR - 1) return;
+  if (n - b0 != NR - 1) return;
   zd ct[NR], cs[NR], tp, sp;
   ring_coeffs<NR>(A.ha + (long long)rhs * NR, A.hb + (long long)rhs * NR, b0, n, ct, cs, tp, sp);
   cplx<T>* S = A.fold_s + rhs * A.fold_stride;
@@ -1016,52 +925,13 @@ __global__ void __launch_bounds__(256) k_ring_fold(ModeArgsZ<T> A, long long vol
   }
 }
 
-// The new base of the folded right-hand sides, and the change of phase (after
-// every block of k_ring_fold and the turn has read the old ones).
-__global__ void k_ring_rebase(ModalScal* sc, const int* active, int nact, int nr, int short_steps) {
+// The new base of the folded right-hand sides (after every block of
+// k_ring_fold has read the old one).
+__global__ void k_ring_rebase(ModalScal* sc, const int* active, int nact, int nr) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nact) return;
   ModalScal& s = sc[rhs_of(active, i)];
-  const int n = s.step + 1;
-  if (s.phase != 0 || n - s.base != nr - 1) return;
-  s.base = n;
-  if (n == short_steps) {
-    s.phase = 1;
-    s.rslot = n % nr;
-  }
-}
-
-// Scalars of the next step of the right-hand sides with a stored direction
-// (one wavefront each): beta, and tau = s^T p of p = z + beta p_old.
-__global__ void __launch_bounds__(64) k_direction_scalars(ModalScal* sc, const double* __restrict__ part, int nmb,
-                                                          const int* __restrict__ active) {
-  const int rhs = rhs_of(active, blockIdx.x), t = threadIdx.x;
-  ModalScal& s = sc[rhs];
-  if (s.phase == 0) return;
-  // 9 strided sums of each value, then those in order
-  double v = 0;
-  if (t < 9 * MODAL_PART) {
-#pragma unroll 4
-    for (int k = t / MODAL_PART; k < nmb; k += 9) v += part[((long long)rhs * nmb + k) * MODAL_PART + t % MODAL_PART];
-  }
-  double a[MODAL_PART];
-  for (int k = 0; k < MODAL_PART; ++k) {
-    a[k] = 0;
-    for (int j = 0; j < 9; ++j) a[k] += __shfl(v, j * MODAL_PART + k);
-  }
-  if (t != 0) return;
-  const zd rho = mk(a[0], a[1]), sigma = mk(a[2], a[3]), rho_old = s.rho;
-  const zd tau_old = s.phase == 1 ? mk(a[5], a[6]) : s.tau;
-  zd beta;
-  if (!quotient(rho, rho_old, beta)) s.flag = 1;
-  s.rho_old = rho_old;
-  s.rho = rho;
-  s.sigma = sigma;
-  s.n2 = a[4];
-  s.beta = beta;
-  s.tau = rho + 2.0 * (beta * sigma) + beta * beta * tau_old;
-  s.step += 1;
-  s.phase = 2;
+  if (s.step + 1 - s.base == nr - 1) s.base = s.step + 1;
 }
 
 // |r|^2 and the breakdown flag of the last mode pass per right-hand side,
@@ -1131,8 +1001,6 @@ void plane_reg(iobm_ctx c, int mode, const PlaneArgs<T>& A) {
     case PM_INV: IOBM_PR(PM_INV); break;
     case PM_VFWD: IOBM_PR(PM_VFWD); break;
     case PM_FWD: IOBM_PR(PM_FWD); break;
-    case PM_DFULL: IOBM_PR(PM_DFULL); break;
-    case PM_DINV: IOBM_PR(PM_DINV); break;
     default: IOBM_PR(PM_ACC); break;
   }
 #undef IOBM_PR
@@ -1162,8 +1030,6 @@ hipError_t launch_plane(iobm_ctx c, int mode, const PlaneArgs<T>& A) {
     case PM_INV: IOBM_PL(PM_INV); break;
     case PM_VFWD: IOBM_PL(PM_VFWD); break;
     case PM_FWD: IOBM_PL(PM_FWD); break;
-    case PM_DFULL: IOBM_PL(PM_DFULL); break;
-    case PM_DINV: IOBM_PL(PM_DINV); break;
     default: IOBM_PL(PM_ACC); break;
   }
 #undef IOBM_PL
@@ -1194,8 +1060,6 @@ hipError_t launch_zstep(iobm_ctx c, int mode, const ModeArgsZ<T>& A, int nact) {
   switch (mode) {                                    \
     case ZS_STEP: IOBM_Z1(NFF, ZS_STEP, BB); break;   \
     case ZS_START: IOBM_Z1(NFF, ZS_START, BB); break; \
-    case ZS_TURN: IOBM_Z1(NFF, ZS_TURN, BB); break;   \
-    case ZS_DSTEP: IOBM_Z1(NFF, ZS_DSTEP, BB); break; \
     default: IOBM_Z1(NFF, ZS_FOLD, BB); break;        \
   }
 #define IOBM_Z3(BB)                    \
@@ -1269,7 +1133,6 @@ static PlaneArgs<T> plane_args(iobm_ctx c, const Modal<T>& M, cplx<T>* vec, int 
   A.sc = M.sc;
   A.part = M.part;
   A.dpart = M.dpart;
-  for (int i = 0; i < ModalRing<T>::n; ++i) A.ring[i] = M.ring[i];
   return A;
 }
 
@@ -1288,19 +1151,15 @@ hipError_t modal_start(iobm_ctx c, const Modal<T>& M, int nact, const int* activ
 }
 
 template <typename T>
-hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active, const ModalPlan& plan) {
+hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active, bool fold) {
   if (nact <= 0) return hipSuccess;
   const double stream = (double)nact * c->g.npts * sizeof(cplx<T>);
-  hipError_t e = hipSuccess;
   PlaneArgs<T> P = plane_args<T>(c, M, M.w, nact, active);
   const ModeArgsZ<T> A = mode_args<T>(c, M, active);
   const bool kb = c->kb.ncen > 0;
-  if (plan.slowp)
-    hipLaunchKernelGGL(k_direction_scalars, dim3(nact), dim3(64), 0, c->stream, M.sc, M.part, M.nmb, active);
   int rec = prof_start(c, kb ? IOBM_K_FFT_PLANES : IOBM_K_FFT_PLANES_UPD);
-  if (plan.fastp) e = launch_plane<T>(c, kb ? PM_INV : PM_FULL, P);
-  if (e == hipSuccess && plan.slowp) e = launch_plane<T>(c, kb ? PM_DINV : PM_DFULL, P);
-  prof_stop(c, rec, (plan.slowp ? 4.0 : 2.0) * stream);
+  hipError_t e = launch_plane<T>(c, kb ? PM_INV : PM_FULL, P);
+  prof_stop(c, rec, 2.0 * stream);
   if (e != hipSuccess) return e;
   if (kb) {
     // C = B^T z, W = h^3 D C, and C^T W as one more partial of z^T V z
@@ -1312,19 +1171,14 @@ hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active
     if (e != hipSuccess) return e;
   }
   rec = prof_start(c, IOBM_K_ZFILTER);
-  if (plan.fastp) e = launch_zstep<T>(c, ZS_STEP, A, nact);
-  if (e == hipSuccess && plan.slowp) e = launch_zstep<T>(c, ZS_DSTEP, A, nact);
-  prof_stop(c, rec, (plan.slowp ? 8.0 : 5.0) * stream);
-  if (e != hipSuccess || !(plan.fold || plan.turn)) return e;
+  e = launch_zstep<T>(c, ZS_STEP, A, nact);
+  prof_stop(c, rec, 5.0 * stream);
+  if (e != hipSuccess || !fold) return e;
   const long long vol = c->g.npts;
   const unsigned bx = (unsigned)std::min<long long>(256, (vol + 255) / 256);
   hipLaunchKernelGGL(k_ring_fold<T>, dim3(bx, nact), dim3(256), 0, c->stream, A, vol);
-  if (plan.turn) {
-    e = launch_zstep<T>(c, ZS_TURN, A, nact);
-    if (e != hipSuccess) return e;
-  }
   hipLaunchKernelGGL(k_ring_rebase, dim3((nact + 255) / 256), dim3(256), 0, c->stream, M.sc, active, nact,
-                     (int)ModalRing<T>::n, modal_short_steps<T>());
+                     (int)ModalRing<T>::n);
   return hipGetLastError();
 }
 
@@ -1357,7 +1211,7 @@ hipError_t modal_check(iobm_ctx c, const Modal<T>& M, int nact, const int* activ
 #define IOBM_MODAL_INST(T)                                                                                       \
   template hipError_t modal_setup<T>(iobm_ctx, Modal<T>&);                                                       \
   template hipError_t modal_start<T>(iobm_ctx, const Modal<T>&, int, const int*);                                \
-  template hipError_t modal_step<T>(iobm_ctx, const Modal<T>&, int, const int*, const ModalPlan&);                           \
+  template hipError_t modal_step<T>(iobm_ctx, const Modal<T>&, int, const int*, bool);                           \
   template hipError_t modal_correct<T>(iobm_ctx, const Modal<T>&, zd*, const int*, int, const int*, double, int); \
   template hipError_t modal_check<T>(iobm_ctx, const Modal<T>&, int, const int*, double*, int*);
 IOBM_MODAL_INST(float)
