@@ -39,7 +39,6 @@ struct ModeArgs {
   // kappa_x h_x and kappa_y h_y (Eqs. (12)-(13) at G + kappa); 0 by default
   double tx = 0, ty = 0;
 };
-__host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeData* out);
 
 struct KBData {
   int ncen = 0, rank = 0, nproj = 0;

@@ -954,16 +954,19 @@ __global__ void __launch_bounds__(256) k_modal_check(const ModalScal* __restrict
 // Filter table [energy][3 nf + nf^2][mode] in the iteration precision:
 // al_k = -q_(nf-1-k), fb_k, fbb_k, and the state propagator M^L of
 // (F(z), F(z-1), ...), formed in FP64.
-template <typename T>
-__global__ void __launch_bounds__(128) k_filter_table(int nE, int nxy, int nf, int L, const ModeData* __restrict__ modes,
-                                                      cplx<T>* __restrict__ ft) {
+// The order is a template argument so that the matrices stay in registers.
+template <typename T, int nf>
+__global__ void __launch_bounds__(64) k_filter_table(int nE, int nxy, int L, const ModeData* __restrict__ modes,
+                                                     cplx<T>* __restrict__ ft) {
   const long long g = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (g >= (long long)nE * nxy) return;
   const int e = (int)(g / nxy), m = (int)(g - (long long)e * nxy);
   const ModeData& md = modes[g];
   cplx<T>* o = ft + (long long)e * (3 * nf + nf * nf) * nxy + m;
-  zd M[9], P[9], t[9];
+  zd M[nf * nf], P[nf * nf], t[nf * nf];
+#pragma unroll
   for (int i = 0; i < nf * nf; ++i) M[i] = mk(0.0, 0.0);
+#pragma unroll
   for (int k = 0; k < nf; ++k) {
     M[k] = -md.q[nf - 1 - k];
     if (k > 0) M[k * nf + k - 1] = mk(1.0, 0.0);
@@ -971,16 +974,22 @@ __global__ void __launch_bounds__(128) k_filter_table(int nE, int nxy, int nf, i
     o[(long long)(nf + k) * nxy] = cvt<T>(md.fb[k]);
     o[(long long)(2 * nf + k) * nxy] = cvt<T>(md.fbb[k]);
   }
+#pragma unroll
   for (int i = 0; i < nf * nf; ++i) P[i] = M[i];
   for (int p = 1; p < L; p *= 2) {  // L is a power of two
+#pragma unroll
     for (int i = 0; i < nf; ++i)
+#pragma unroll
       for (int j = 0; j < nf; ++j) {
         zd s = mk(0.0, 0.0);
+#pragma unroll
         for (int k = 0; k < nf; ++k) s = s + P[i * nf + k] * P[k * nf + j];
         t[i * nf + j] = s;
       }
+#pragma unroll
     for (int i = 0; i < nf * nf; ++i) P[i] = t[i];
   }
+#pragma unroll
   for (int i = 0; i < nf * nf; ++i) o[(long long)(3 * nf + i) * nxy] = cvt<T>(P[i]);
 }
 
@@ -1090,8 +1099,15 @@ int modal_mode_blocks(iobm_ctx c) {
 template <typename T>
 hipError_t modal_setup(iobm_ctx c, Modal<T>& M) {
   const long long n = (long long)M.nE * c->g.nxy;
-  hipLaunchKernelGGL(k_filter_table<T>, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, c->stream, M.nE, c->g.nxy,
-                     c->g.nf, kModalChunk, c->modes_d, M.ft);
+  const dim3 grid((unsigned)((n + 63) / 64)), blk(64);
+#define IOBM_FT(NFF) \
+  hipLaunchKernelGGL((k_filter_table<T, NFF>), grid, blk, 0, c->stream, M.nE, c->g.nxy, kModalChunk, c->modes_d, M.ft)
+  switch (c->g.nf) {
+    case 1: IOBM_FT(1); break;
+    case 2: IOBM_FT(2); break;
+    default: IOBM_FT(3); break;
+  }
+#undef IOBM_FT
   return hipGetLastError();
 }
 

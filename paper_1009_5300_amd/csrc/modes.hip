@@ -126,68 +126,89 @@ IOBM_HD zd polish(const double* pc, int deg, zd c) {
   return c;
 }
 
-// Small complex Gaussian elimination with partial pivoting, n <= 3.
-IOBM_HD bool csolve(zd* A, zd* b, int n) {
-  for (int k = 0; k < n; ++k) {
+// The small dense steps below have compile-time sizes and no run-time index:
+// rows and roots picked at run time go through selects, so that everything
+// stays in registers.
+
+// Small complex Gaussian elimination with partial pivoting, N <= 3.
+template <int N>
+IOBM_HD bool csolve(zd* A, zd* b) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
     int p = k;
-    double best = cabs_(A[k * n + k]);
-    for (int i = k + 1; i < n; ++i) {
-      double v = cabs_(A[i * n + k]);
+    double best = cabs_(A[k * N + k]);
+#pragma unroll
+    for (int i = k + 1; i < N; ++i) {
+      const double v = cabs_(A[i * N + k]);
       if (v > best) { best = v; p = i; }
     }
     if (best == 0) return false;
-    if (p != k) {
-      for (int j = 0; j < n; ++j) { zd t = A[k * n + j]; A[k * n + j] = A[p * n + j]; A[p * n + j] = t; }
-      zd t = b[k]; b[k] = b[p]; b[p] = t;
+#pragma unroll
+    for (int i = k + 1; i < N; ++i) {
+      if (p != i) continue;
+#pragma unroll
+      for (int j = 0; j < N; ++j) { const zd t = A[k * N + j]; A[k * N + j] = A[i * N + j]; A[i * N + j] = t; }
+      const zd t = b[k]; b[k] = b[i]; b[i] = t;
     }
-    for (int i = k + 1; i < n; ++i) {
-      zd f = cdiv(A[i * n + k], A[k * n + k]);
-      for (int j = k; j < n; ++j) A[i * n + j] = A[i * n + j] - f * A[k * n + j];
+#pragma unroll
+    for (int i = k + 1; i < N; ++i) {
+      const zd f = cdiv(A[i * N + k], A[k * N + k]);
+#pragma unroll
+      for (int j = k; j < N; ++j) A[i * N + j] = A[i * N + j] - f * A[k * N + j];
       b[i] = b[i] - f * b[k];
     }
   }
-  for (int k = n - 1; k >= 0; --k) {
-    zd s = b[k];
-    for (int j = k + 1; j < n; ++j) s = s - A[k * n + j] * b[j];
-    b[k] = cdiv(s, A[k * n + k]);
+#pragma unroll
+  for (int k = N - 1; k >= 0; --k) {
+    zd t = b[k];
+#pragma unroll
+    for (int j = k + 1; j < N; ++j) t = t - A[k * N + j] * b[j];
+    b[k] = cdiv(t, A[k * N + k]);
   }
   return true;
 }
 
-// Coefficients (ascending, monic implied) of prod_{j != skip} (x - r_j) over n nodes.
-IOBM_HD void poly_from_roots(const zd* r, int n, int skip, zd* coef, int* deg) {
-  zd p[4] = {mk(1.0, 0.0), mk(0.0, 0.0), mk(0.0, 0.0), mk(0.0, 0.0)};
-  int d = 0;
-  for (int j = 0; j < n; ++j) {
+// Coefficients (ascending, coef[0 .. N]) of prod_{j != skip} (x - r_j) over N nodes.
+template <int N>
+IOBM_HD void poly_from_roots(const zd* r, int skip, zd* coef) {
+  coef[0] = mk(1.0, 0.0);
+#pragma unroll
+  for (int k = 1; k <= N; ++k) coef[k] = mk(0.0, 0.0);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
     if (j == skip) continue;
     // p(x) *= (x - r_j)
-    for (int k = d + 1; k >= 1; --k) p[k] = p[k - 1] - r[j] * p[k];
-    p[0] = -(r[j] * p[0]);
-    ++d;
+#pragma unroll
+    for (int k = N; k >= 1; --k) coef[k] = coef[k - 1] - r[j] * coef[k];
+    coef[0] = -(r[j] * coef[0]);
   }
-  for (int k = 0; k <= d; ++k) coef[k] = p[k];
-  *deg = d;
 }
 
-// Lagrange row: coefficients L_m (m < n) of the basis polynomial that is 1 at
+// Lagrange row: coefficients L_m (m < N) of the basis polynomial that is 1 at
 // node r[p] and 0 at the other nodes.
-IOBM_HD void lagrange_row(const zd* r, int n, int p, zd* L) {
-  zd coef[4];
-  int deg;
-  poly_from_roots(r, n, p, coef, &deg);
-  zd den = mk(1.0, 0.0);
-  for (int j = 0; j < n; ++j)
-    if (j != p) den = den * (r[p] - r[j]);
-  for (int m = 0; m < n; ++m) L[m] = m <= deg ? cdiv(coef[m], den) : mk(0.0, 0.0);
+template <int N>
+IOBM_HD void lagrange_row(const zd* r, int p, zd* L) {
+  zd coef[N + 1], rp = r[0], den = mk(1.0, 0.0);
+  poly_from_roots<N>(r, p, coef);
+#pragma unroll
+  for (int j = 1; j < N; ++j)
+    if (j == p) rp = r[j];
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if (j != p) den = den * (rp - r[j]);
+#pragma unroll
+  for (int m = 0; m < N; ++m) L[m] = cdiv(coef[m], den);
 }
 
-}  // namespace
-
-__host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeData* out) {
-  const int nf = A.nf;
+// One mode of one energy.  The order is a template argument: with a run-time
+// order every small array is indexed at run time and lives in scratch memory.
+template <int nf>
+__device__ __forceinline__ void compute_mode(const ModeArgs& A, double E, int m, ModeData* out) {
   const double* c = A.c;
   ModeData md;
+#pragma unroll
   for (int i = 0; i < 9; ++i) md.sig[i] = mk(0.0, 0.0);
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
     md.q[i] = md.fb[i] = md.fbb[i] = md.lr[i] = md.ll[i] = md.btil[i] = mk(0.0, 0.0);
   }
@@ -203,6 +224,7 @@ __host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeDa
   // (G_nu + kappa) h per direction
   const double thx = 2.0 * M_PI * nux / A.nx + A.tx, thy = 2.0 * M_PI * nuy / A.ny + A.ty;
   double ex = c[0], ey = c[0];
+#pragma unroll
   for (int n = 1; n <= nf; ++n) {
     ex += 2.0 * c[n] * cos(n * thx);
     ey += 2.0 * c[n] * cos(n * thy);
@@ -226,11 +248,13 @@ __host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeDa
   } else {
     cubic_roots(pc[2] / pc[3], pc[1] / pc[3], pc[0] / pc[3], croot);
   }
+#pragma unroll
   for (int j = 0; j < nf; ++j) croot[j] = polish(pc, nf, croot[j]);
 
   // outgoing root of each pair
   zd x[3];
   int prop = -1;
+#pragma unroll
   for (int j = 0; j < nf; ++j) {
     zd cc = croot[j];
     bool real = fabs(cc.im) <= 1e-14 * fmax(1.0, fabs(cc.re));
@@ -251,65 +275,90 @@ __host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeDa
   // monic outgoing polynomial
   {
     zd coef[4];
-    int deg;
-    poly_from_roots(x, nf, -1, coef, &deg);
+    poly_from_roots<nf>(x, -1, coef);
+#pragma unroll
     for (int k = 0; k < nf; ++k) md.q[k] = coef[k];
   }
   // companion matrix M (state = values on nf consecutive planes)
   zd Mc[9], Mp[9], tmp[9];
+#pragma unroll
   for (int i = 0; i < nf * nf; ++i) Mc[i] = mk(0.0, 0.0);
+#pragma unroll
   for (int i = 0; i + 1 < nf; ++i) Mc[i * nf + i + 1] = mk(1.0, 0.0);
+#pragma unroll
   for (int k = 0; k < nf; ++k) Mc[(nf - 1) * nf + k] = -md.q[k];
   // Mp = M^nf
+#pragma unroll
   for (int i = 0; i < nf * nf; ++i) Mp[i] = mk((i % (nf + 1)) == 0 ? 1.0 : 0.0, 0.0);
+#pragma unroll
   for (int p = 0; p < nf; ++p) {
+#pragma unroll
     for (int i = 0; i < nf; ++i)
+#pragma unroll
       for (int j = 0; j < nf; ++j) {
         zd s = mk(0.0, 0.0);
+#pragma unroll
         for (int k = 0; k < nf; ++k) s = s + Mp[i * nf + k] * Mc[k * nf + j];
         tmp[i * nf + j] = s;
       }
+#pragma unroll
     for (int i = 0; i < nf * nf; ++i) Mp[i] = tmp[i];
   }
   double a[4];
+#pragma unroll
   for (int n = 0; n <= nf; ++n) a[n] = -c[n] / (2.0 * hz2);
   // Sigma_R = W M^nf, W[i][m] = a_{nf+m-i} for m <= i
+#pragma unroll
   for (int i = 0; i < nf; ++i)
+#pragma unroll
     for (int j = 0; j < nf; ++j) {
       zd s = mk(0.0, 0.0);
+#pragma unroll
       for (int mm = 0; mm <= i; ++mm) s = s + a[nf + mm - i] * Mp[mm * nf + j];
       md.sig[i * nf + j] = s;
     }
 
   // flat-wire Green's function: u_k^T = e_0^T M^k, k = 0..2nf
   zd U[7][3];
+#pragma unroll
   for (int j = 0; j < nf; ++j) U[0][j] = mk(j == 0 ? 1.0 : 0.0, 0.0);
+#pragma unroll
   for (int k = 1; k <= 2 * nf; ++k)
+#pragma unroll
     for (int j = 0; j < nf; ++j) {
       zd s = mk(0.0, 0.0);
+#pragma unroll
       for (int l = 0; l < nf; ++l) s = s + U[k - 1][l] * Mc[l * nf + j];
       U[k][j] = s;
     }
   // rows d = 0..nf-1: sum_n A_n G(|d - n|) = delta_d0, A_0 = dE - a_0, A_n = -a_|n|
   zd K[9], g[3];
+#pragma unroll
   for (int d = 0; d < nf; ++d) {
+#pragma unroll
     for (int j = 0; j < nf; ++j) K[d * nf + j] = mk(0.0, 0.0);
+#pragma unroll
     for (int n = -nf; n <= nf; ++n) {
       double An = n == 0 ? dE - a[0] : -a[n < 0 ? -n : n];
       int dist = d - n < 0 ? n - d : d - n;
+#pragma unroll
       for (int j = 0; j < nf; ++j) K[d * nf + j] = K[d * nf + j] + An * U[dist][j];
     }
     g[d] = mk(d == 0 ? 1.0 : 0.0, 0.0);
   }
-  if (!csolve(K, g, nf)) md.flags |= MODE_FAIL;
+  if (!csolve<nf>(K, g)) md.flags |= MODE_FAIL;
   zd G[4];
+#pragma unroll
   for (int d = 0; d <= nf; ++d) {
     zd s = mk(0.0, 0.0);
+#pragma unroll
     for (int j = 0; j < nf; ++j) s = s + U[d][j] * g[j];
     G[d] = s;
   }
+#pragma unroll
   for (int d = 0; d < nf; ++d) {
     zd s0 = G[d], s1 = G[d + 1];
+#pragma unroll
     for (int k = 1; k <= d; ++k) {
       s0 = s0 + md.q[nf - k] * G[d - k];
       s1 = s1 + md.q[nf - k] * G[d + 1 - k];
@@ -320,25 +369,34 @@ __host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeDa
 
   if (prop >= 0) {
     md.flags |= MODE_OPEN;
-    zd xp = x[prop];
+    zd xp = x[0];
+#pragma unroll
+    for (int j = 1; j < nf; ++j)
+      if (j == prop) xp = x[j];
     md.xp = xp;
     double v = 0;
+#pragma unroll
     for (int n = 1; n <= nf; ++n) v += n * c[n] * cpow_(xp, n).im;
     md.v = v / A.hz;
     if (!(md.v > 0)) md.flags |= MODE_FAIL;
-    lagrange_row(x, nf, prop, md.lr);
+    lagrange_row<nf>(x, prop, md.lr);
     zd y[3];
+#pragma unroll
     for (int j = 0; j < nf; ++j) y[j] = cdiv(mk(1.0, 0.0), x[j]);
-    lagrange_row(y, nf, prop, md.ll);
+    lagrange_row<nf>(y, prop, md.ll);
     zd kin = mk(0.0, 0.0);
+#pragma unroll
     for (int mm = 0; mm < nf; ++mm) kin = kin + md.ll[mm] * cpow_(xp, mm);
     md.kin = kin;
     // right-hand side profile, planes i = 0..nf-1:
     //   sum_{m>=1, i+m<=nf} a_{i+m} xp^{-m} - sum_j SigmaL[i][j] xp^j,
     //   SigmaL[i][j] = SigmaR[nf-1-i][nf-1-j]
+#pragma unroll
     for (int i = 0; i < nf; ++i) {
       zd s = mk(0.0, 0.0);
+#pragma unroll
       for (int mm = 1; i + mm <= nf; ++mm) s = s + a[i + mm] * cpow_(xp, -mm);
+#pragma unroll
       for (int j = 0; j < nf; ++j) s = s - md.sig[(nf - 1 - i) * nf + (nf - 1 - j)] * cpow_(xp, j);
       md.btil[i] = s;
     }
@@ -346,8 +404,8 @@ __host__ __device__ void compute_mode(const ModeArgs& A, double E, int m, ModeDa
   *out = md;
 }
 
-namespace {
-__global__ void k_modes(ModeArgs A, const double* __restrict__ Elist, const double* __restrict__ kap,
+template <int NF>
+__global__ void __launch_bounds__(64) k_modes(ModeArgs A, const double* __restrict__ Elist, const double* __restrict__ kap,
                         ModeData* __restrict__ out) {
   const int nxy = A.nx * A.ny;
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -358,7 +416,7 @@ __global__ void k_modes(ModeArgs A, const double* __restrict__ Elist, const doub
     A.tx = kap[2 * e];
     A.ty = kap[2 * e + 1];
   }
-  compute_mode(A, Elist[e], m, &out[gid]);
+  compute_mode<NF>(A, Elist[e], m, &out[gid]);
 }
 }  // namespace
 
@@ -373,9 +431,12 @@ hipError_t launch_modes(iobm_ctx ctx, const double* E_d, int nE, ModeData* out, 
   A.hz = ctx->g.hz;
   for (int i = 0; i < 4; ++i) A.c[i] = ctx->c[i];
   long long n = (long long)ctx->g.nxy * nE;
-  int threads = 128;
-  long long blocks = (n + threads - 1) / threads;
-  hipLaunchKernelGGL(k_modes, dim3((unsigned)blocks), dim3(threads), 0, ctx->stream, A, E_d, kap_d, out);
+  const dim3 grid((unsigned)((n + 63) / 64)), blk(64);
+  switch (A.nf) {
+    case 1: hipLaunchKernelGGL(k_modes<1>, grid, blk, 0, ctx->stream, A, E_d, kap_d, out); break;
+    case 2: hipLaunchKernelGGL(k_modes<2>, grid, blk, 0, ctx->stream, A, E_d, kap_d, out); break;
+    default: hipLaunchKernelGGL(k_modes<3>, grid, blk, 0, ctx->stream, A, E_d, kap_d, out); break;
+  }
   return hipGetLastError();
 }
 
