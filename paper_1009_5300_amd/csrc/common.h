@@ -89,6 +89,21 @@ __device__ __forceinline__ void dft_small(cplx<T>* v, const cplx<T>* tw, int n, 
     v[0] = v[0] + t;
     v[1] = m + js;
     v[2] = m - js;
+  } else if constexpr (R == 5) {
+    // cos and sin of 72 and 144 degrees
+    const T c1 = (T)0.30901699437494742410229341718282, c2 = (T)-0.80901699437494742410229341718282;
+    const T s1 = (T)0.95105651629515357211643933337938, s2 = (T)0.58778525229247312916870595463907;
+    const cplx<T> t1 = v[1] + v[4], t2 = v[2] + v[3], d1 = v[1] - v[4], d2 = v[2] - v[3];
+    const cplx<T> m1 = v[0] + c1 * t1 + c2 * t2, m2 = v[0] + c2 * t1 + c1 * t2;
+    const cplx<T> n1 = s1 * d1 + s2 * d2, n2 = s2 * d1 - s1 * d2;
+    // forward subtracts i n from the first of each pair, inverse adds it
+    const cplx<T> j1 = sign < 0 ? mk(n1.im, -n1.re) : mk(-n1.im, n1.re);
+    const cplx<T> j2 = sign < 0 ? mk(n2.im, -n2.re) : mk(-n2.im, n2.re);
+    v[0] = v[0] + t1 + t2;
+    v[1] = m1 + j1;
+    v[2] = m2 + j2;
+    v[3] = m2 - j2;
+    v[4] = m1 - j1;
   } else {
     cplx<T> in[R];
 #pragma unroll
@@ -112,17 +127,22 @@ __device__ __forceinline__ int small_quotient(int a, float inv) { return (int)((
 // One Stockham pass of radix R over `count` independent 1D transforms of
 // length n; element e of transform t lives at t*tstride + e*estride.  Ns is
 // the length of the sub-transforms already completed by earlier passes.
+// Consecutive threads take consecutive elements of a contiguous transform, and
+// neighbouring transforms where those are contiguous (tstride = 1): elements
+// nx apart share LDS banks (nx = 36, complex128: 16 lanes on one bank).
 template <typename T, int R>
-__device__ void stockham_pass_r(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out, int n,
+__device__ __forceinline__ void stockham_pass_r(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out, int n,
                                 int Ns, int count, int estride, int tstride, const cplx<T>* tw,
                                 int sign) {
   const int per = n / R;
   const int total = count * per;
   const int tstep = n / (Ns * R);
-  const float iper = 1.0f / (float)per, ins = 1.0f / (float)Ns;
+  const bool cols = tstride == 1;
+  const int fast = cols ? count : per;
+  const float ifast = 1.0f / (float)fast, ins = 1.0f / (float)Ns;
   for (int w = threadIdx.x; w < total; w += blockDim.x) {
-    const int t = small_quotient(w, iper);
-    const int j = w - t * per;
+    const int hi = small_quotient(w, ifast), lo = w - hi * fast;
+    const int t = cols ? lo : hi, j = cols ? hi : lo;
     const int base = t * tstride;
     const int q = small_quotient(j, ins) * Ns;
     const int k = j - q;
@@ -143,7 +163,7 @@ __device__ void stockham_pass_r(const cplx<T>* __restrict__ in, cplx<T>* __restr
 // Generic odd-prime radix (up to 31): O(R^2) butterfly, slow path for
 // lateral sizes with unusual prime factors.
 template <typename T>
-__device__ void stockham_pass_generic(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out,
+__device__ __forceinline__ void stockham_pass_generic(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out,
                                       int n, int R, int Ns, int count, int estride, int tstride,
                                       const cplx<T>* tw, int sign) {
   const int per = n / R;
@@ -151,8 +171,8 @@ __device__ void stockham_pass_generic(const cplx<T>* __restrict__ in, cplx<T>* _
   const int tstep = n / (Ns * R);
   const int stride = n / R;
   for (int w = threadIdx.x; w < total; w += blockDim.x) {
-    const int t = w / per;
-    const int j = w - t * per;
+    const int t = tstride == 1 ? w % count : w / per;
+    const int j = tstride == 1 ? w / count : w - t * per;
     const int base = t * tstride;
     const int k = j % Ns;
     const int idxD = (j / Ns) * Ns * R + k;
@@ -183,7 +203,7 @@ __device__ __forceinline__ void stockham_pass(const cplx<T>* __restrict__ in,
 }
 
 template <typename T>
-__device__ cplx<T>* fft2d_lds(cplx<T>* a, cplx<T>* b, const FFTPlan2D& p, const cplx<T>* twx,
+__device__ __forceinline__ cplx<T>* fft2d_lds(cplx<T>* a, cplx<T>* b, const FFTPlan2D& p, const cplx<T>* twx,
                               const cplx<T>* twy, int sign) {
   const int nx = p.x.n, ny = p.y.n;
   cplx<T>* src = a;
@@ -204,6 +224,20 @@ __device__ cplx<T>* fft2d_lds(cplx<T>* a, cplx<T>* b, const FFTPlan2D& p, const 
   }
   return src;
 }
+
+// nf planes of nxy values and one spare in LDS, transformed one after the
+// other: fft2d_lds leaves the result of an odd number of passes in its second
+// buffer, so that with the spare as that buffer plane k moves to slot(k).  The
+// slots are numbers, not pointers: a table of pointers hides from the compiler
+// that they point into LDS (flat accesses, the table itself in scratch).
+struct FaceSlots {
+  int nf;
+  bool odd;
+  __device__ FaceSlots(const FFTPlan2D& p, int n) : nf(n), odd((p.x.nstages + p.y.nstages) & 1) {}
+  __device__ int slot(int k) const { return odd ? (k ? k - 1 : nf) : k; }   // after the first transform
+  __device__ int free_before(int k) const { return odd && k ? k - 1 : nf; }  // the spare while plane k is transformed
+  __device__ int spare() const { return odd ? nf - 1 : nf; }                // once every plane is
+};
 
 // ------------------------------------------------ in-register 1D FFT ------
 // Length-N transform held in registers (N known at compile time), same

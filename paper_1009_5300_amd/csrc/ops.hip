@@ -5,6 +5,7 @@
 // Layout: a batch of right-hand sides is [rhs][z][y][x] interleaved complex
 // (complex64 or complex128), x fastest.  Kernels that work on a subset of
 // the batch take `active` (slot -> rhs id) and are launched over the slots.
+#include "fftreg.h"
 #include "internal.h"
 
 namespace {
@@ -546,8 +547,8 @@ template <> struct Pair<double> {
 // of x^T (its change of y) goes to part[rhs][pslot + side].  With rout set
 // (the refinement residual), y holds b - A_st x on the faces and the block
 // writes rout = y + Sigma x in precision TR and the partial of |rout|^2.
-template <typename T, typename TR>
-__global__ void k_boundary(FFTPlan2D plan, int nz, int nf, const cplx<T>* __restrict__ x,
+template <typename T, typename TR, int nf>
+__global__ void k_boundary(FFTPlan2D plan, int nz, const cplx<T>* __restrict__ x,
                            cplx<T>* __restrict__ y, cplx<TR>* __restrict__ rout,
                            const cplx<T>* __restrict__ sig,
                            const int* __restrict__ e_rhs, const cplx<T>* __restrict__ twx,
@@ -556,51 +557,55 @@ __global__ void k_boundary(FFTPlan2D plan, int nz, int nf, const cplx<T>* __rest
   extern __shared__ char smem_raw[];
   cplx<T>* buf = reinterpret_cast<cplx<T>*>(smem_raw);
   const int nxy = plan.x.n * plan.y.n;
-  const cplx<T>*tx = twx, *ty = twy;
+  cplx<T>*tx = buf + (nf + 1) * nxy, *ty = tx + plan.x.n;
   if (tw_lds) {  // twiddle tables beside the planes, where the LDS holds both
-    cplx<T>* t = buf + (nf + 1) * nxy;
-    for (int i = threadIdx.x; i < plan.x.n; i += blockDim.x) t[i] = twx[i];
-    for (int i = threadIdx.x; i < plan.y.n; i += blockDim.x) t[plan.x.n + i] = twy[i];
-    tx = t;
-    ty = t + plan.x.n;
+    for (int i = threadIdx.x; i < plan.x.n; i += blockDim.x) tx[i] = twx[i];
+    for (int i = threadIdx.x; i < plan.y.n; i += blockDim.x) ty[i] = twy[i];
   }
   const int slot = blockIdx.x >> 1;
   const int side = blockIdx.x & 1;
   const int rhs = rhs_of(active, slot);
   const long long vol = (long long)nxy * nz;
   const cplx<T>* sg = sig + (long long)e_rhs[rhs] * nf * nf * nxy;  // [k][mode]
-  cplx<T>* P[4];
-  for (int k = 0; k <= nf; ++k) P[k] = buf + k * nxy;
+  const FaceSlots F(plan, nf);
+  auto fft = [&](int from, int spare, int sign) {
+    if (tw_lds) fft2d_lds(buf + from * nxy, buf + spare * nxy, plan, tx, ty, sign);
+    else fft2d_lds(buf + from * nxy, buf + spare * nxy, plan, twx, twy, sign);
+  };
   const int pbase = side ? nz - nf : 0;
   for (int k = 0; k < nf; ++k) {
     const cplx<T>* src = x + rhs * vol + (long long)(pbase + k) * nxy;
-    for (int p = threadIdx.x; p < nxy; p += blockDim.x) P[k][p] = src[p];
-    __syncthreads();
-    cplx<T>* res = fft2d_lds(P[k], P[nf], plan, tx, ty, -1);
-    if (res != P[k]) { cplx<T>* t = P[k]; P[k] = P[nf]; P[nf] = t; }
+    for (int p = threadIdx.x; p < nxy; p += blockDim.x) buf[k * nxy + p] = src[p];
   }
+  __syncthreads();
+  for (int k = 0; k < nf; ++k) fft(k, F.free_before(k), -1);
   // mode mixing; plane k of the block <-> boundary-plane index i:
   // right: i = k;  left: i = nf-1-k with the reversed block, i.e. the same
   // matrix indexed by (nf-1-k, nf-1-l).
   const T inv = (T)(1.0 / nxy);
   for (int m = threadIdx.x; m < nxy; m += blockDim.x) {
-    cplx<T> in[3], out[3];
-    for (int k = 0; k < nf; ++k) in[k] = P[k][m];
+    cplx<T> in[nf], out[nf];
+#pragma unroll
+    for (int k = 0; k < nf; ++k) in[k] = buf[F.slot(k) * nxy + m];
+#pragma unroll
     for (int k = 0; k < nf; ++k) {
       cplx<T> s = mk<T>(0, 0);
       const int ik = side ? k : nf - 1 - k;
+#pragma unroll
       for (int l = 0; l < nf; ++l) {
         const int il = side ? l : nf - 1 - l;
         s = s + sg[(long long)(ik * nf + il) * nxy + m] * in[l];
       }
       out[k] = inv * s;
     }
-    for (int k = 0; k < nf; ++k) P[k][m] = out[k];
+#pragma unroll
+    for (int k = 0; k < nf; ++k) buf[F.slot(k) * nxy + m] = out[k];
   }
   __syncthreads();
   double s_re = 0, s_im = 0, s_n2 = 0;
   for (int k = 0; k < nf; ++k) {
-    cplx<T>* res = fft2d_lds(P[k], P[nf], plan, tx, ty, +1);
+    fft(F.slot(k), F.spare(), +1);
+    const cplx<T>* res = buf + (F.odd ? F.spare() : F.slot(k)) * nxy;
     const long long po = rhs * vol + (long long)(pbase + k) * nxy;
     for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
       const cplx<T> r = res[p];
@@ -629,20 +634,27 @@ __global__ void k_boundary(FFTPlan2D plan, int nz, int nf, const cplx<T>* __rest
   }
 }
 
-// Square planes (N x N, N in the register-FFT list): the NF face planes of
+// Square planes (N x N, N in launch_boundary's list): the NF face planes of
 // one side sit in LDS (padded rows); N threads per plane transform its rows
 // and then its columns in registers, both ways.  Same contract as
-// k_boundary.  Block partials are staged in LDS and summed by thread 0 in
-// thread order (blocks can be smaller than a wavefront).
+// k_boundary.  One block per state and face: bound by latency, not by bytes
+// (6 to 40 MB at a few hundred GB/s), so more threads than lines share the
+// loads, the mixing and the stores, and the transforms have their twiddles as
+// literals.  32 x 32 x 2 planes, complex128, 46 states: 25.8 us with 64 threads
+// and twiddle loads, 14.3 us now; 36 x 36, 9 states: 22.3 us as LDS stages, 13.7.  Block partials are staged in LDS and
+// summed in a fixed order (blocks can be smaller than a wavefront).
+template <int N, int NF>
+constexpr int face_threads() {
+  return N * NF <= 64 ? 4 * N * NF : (N * NF <= 96 ? 2 * N * NF : N * NF);
+}
 template <typename T, typename TR, int N, int NF>
-__global__ void __launch_bounds__(N * NF) k_boundary_reg(int nz, const cplx<T>* __restrict__ x,
+__global__ void __launch_bounds__((face_threads<N, NF>())) k_boundary_reg(int nz, const cplx<T>* __restrict__ x,
                                                         cplx<T>* __restrict__ y, cplx<TR>* __restrict__ rout,
                                                         const cplx<T>* __restrict__ sig,
                                                         const int* __restrict__ e_rhs,
-                                                        const cplx<T>* __restrict__ tw,
                                                         const int* __restrict__ active,
                                                         Partial* __restrict__ part, int np, int pslot) {
-  constexpr int NN = N * N, BLK = N * NF;
+  constexpr int NN = N * N, LINES = N * NF, BLK = face_threads<N, NF>();
   typedef typename Pair<T>::type VT;
   constexpr int PE = Pair<T>::n;              // elements per vector access
   constexpr int NV = NF * NN / PE;            // vector accesses of the nf planes
@@ -682,23 +694,27 @@ __global__ void __launch_bounds__(N * NF) k_boundary_reg(int nz, const cplx<T>* 
     }
   }
   __syncthreads();
-  const int k = threadIdx.x / N, li = threadIdx.x - k * N;
-  cplx<T> v[N];
-  auto rows_cols = [&](int sign) {
+  auto rows_cols = [&](auto sign) {
+    const int k = threadIdx.x / N, li = threadIdx.x - k * N;
+    cplx<T> v[N];
+    if (threadIdx.x < LINES) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = sm[k][li][i];
-    reg_fft<T, N>(v, tw, sign);
+      for (int i = 0; i < N; ++i) v[i] = sm[k][li][i];
+      line_fft<T, N, decltype(sign)::value>(v);
 #pragma unroll
-    for (int i = 0; i < N; ++i) sm[k][li][i] = v[i];
+      for (int i = 0; i < N; ++i) sm[k][li][i] = v[i];
+    }
     __syncthreads();
+    if (threadIdx.x < LINES) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = sm[k][i][li];
-    reg_fft<T, N>(v, tw, sign);
+      for (int i = 0; i < N; ++i) v[i] = sm[k][i][li];
+      line_fft<T, N, decltype(sign)::value>(v);
 #pragma unroll
-    for (int i = 0; i < N; ++i) sm[k][i][li] = v[i];
+      for (int i = 0; i < N; ++i) sm[k][i][li] = v[i];
+    }
     __syncthreads();
   };
-  rows_cols(-1);
+  rows_cols(std::integral_constant<int, -1>());
   // mode mixing, mode m = ky N + kx at sm[.][ky][kx]; plane k <-> boundary
   // index i as in k_boundary
   const T inv = (T)(1.0 / NN);
@@ -738,7 +754,7 @@ __global__ void __launch_bounds__(N * NF) k_boundary_reg(int nz, const cplx<T>* 
     }
   }
   __syncthreads();
-  rows_cols(+1);
+  rows_cols(std::integral_constant<int, 1>());
   double s_re = 0, s_im = 0, s_n2 = 0;
 #pragma unroll
   for (int b0 = 0; b0 < EPT; b0 += B5) {
@@ -781,10 +797,18 @@ __global__ void __launch_bounds__(N * NF) k_boundary_reg(int nz, const cplx<T>* 
     red[1][threadIdx.x] = s_im;
     red[2][threadIdx.x] = s_n2;
     __syncthreads();
+    __shared__ double red8[3][8];  // 8 strided sums of each value, then those in order
+    if (threadIdx.x < 24) {
+      const int q = threadIdx.x >> 3, t0 = threadIdx.x & 7;
+      double a = 0;
+      for (int t = t0; t < BLK; t += 8) a += red[q][t];
+      red8[q][t0] = a;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
       Partial P;
       P.re = P.im = P.n2 = P.pad = 0;
-      for (int t = 0; t < BLK; ++t) { P.re += red[0][t]; P.im += red[1][t]; P.n2 += red[2][t]; }
+      for (int t = 0; t < 8; ++t) { P.re += red8[0][t]; P.im += red8[1][t]; P.n2 += red8[2][t]; }
       part[(long long)rhs * np + pslot + side] = P;
     }
   }
@@ -1702,8 +1726,7 @@ __global__ void k_readout(FFTPlan2D plan, int nz, int nf, int side, const zd* __
   const int face = blockIdx.x & 1;
   const long long vol = (long long)nxy * nz;
   const ModeData* md = modes + (long long)e_rhs[rhs] * nxy;
-  zd* P[4];
-  for (int k = 0; k <= nf; ++k) P[k] = buf + k * nxy;
+  const FaceSlots F(plan, nf);
   // plane of index m (m = 0..nf-1) counted from the face: near face of a left
   // incidence is plane m, far face is plane nz-nf+m; mirrored for side 1.
   for (int k = 0; k < nf; ++k) {
@@ -1711,17 +1734,16 @@ __global__ void k_readout(FFTPlan2D plan, int nz, int nf, int side, const zd* __
     if (face == 1) plane = side == 0 ? nz - nf + k : nf - 1 - k;
     else plane = side == 0 ? k : nz - 1 - k;
     const zd* src = x + rhs * vol + (long long)plane * nxy;
-    for (int p = threadIdx.x; p < nxy; p += blockDim.x) P[k][p] = src[p];
-    __syncthreads();
-    zd* res = fft2d_lds(P[k], P[nf], plan, twx, twy, -1);
-    if (res != P[k]) { zd* t = P[k]; P[k] = P[nf]; P[nf] = t; }
+    for (int p = threadIdx.x; p < nxy; p += blockDim.x) buf[k * nxy + p] = src[p];
   }
+  __syncthreads();
+  for (int k = 0; k < nf; ++k) fft2d_lds(buf + k * nxy, buf + F.free_before(k) * nxy, plan, twx, twy, -1);
   const double inv = 1.0 / nxy;
   zd* out = (face == 1 ? amp_far : amp_near) + (long long)rhs * nxy;
   for (int m = threadIdx.x; m < nxy; m += blockDim.x) {
     zd a = mk(0.0, 0.0);
     if (md[m].flags & MODE_OPEN) {
-      for (int k = 0; k < nf; ++k) a = a + (face == 1 ? md[m].lr[k] : md[m].ll[k]) * P[k][m];
+      for (int k = 0; k < nf; ++k) a = a + (face == 1 ? md[m].lr[k] : md[m].ll[k]) * buf[F.slot(k) * nxy + m];
       a = inv * a;
     }
     out[m] = a;
@@ -1903,6 +1925,10 @@ static hipError_t launch_stencil(iobm_ctx c, const Op& op, int nrhs, const doubl
     // shorter chunks, so that there are blocks for every compute unit and no
     // block walks a long chunk alone
     while (zc > 8 && (long long)nrhs * ((c->g.nz + zc - 1) / zc) < 2LL * c->num_cu) zc /= 2;
+    // still less than a block per compute unit: 4 planes, as long as the slots
+    // of the partials last (9 states of 36 x 36 x 80, complex128: 24.4 us with
+    // 90 blocks of 8 planes, 19.7 us with 180 of 4)
+    if (zc == 8 && (long long)nrhs * ((c->g.nz + 7) / 8) < c->num_cu && (c->g.nz + 3) / 4 <= PQ_STENCIL_MAX) zc = 4;
     if (ppt > 0) done = launch_apply25_shape<T, Op>(c, ppt, zc, op, nrhs, E_rhs, active);
   }
   if (!done) {
@@ -1921,8 +1947,8 @@ template <typename T, typename TR, int N>
 static void launch_boundary_reg(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx<TR>* rout, int nrhs,
                                 const int* e_rhs, const ModeData* modes, const int* active, Partial* part) {
 #define IOBM_BREG(NF)                                                                                         \
-  hipLaunchKernelGGL((k_boundary_reg<T, TR, N, NF>), dim3(2 * nrhs), dim3(N * NF), 0, c->stream, c->g.nz, x, y, \
-                     rout, sigtab<T>(c), e_rhs, twx<T>(c), active, part, (int)PQ_SLOTS, (int)PQ_BOUNDARY)
+  hipLaunchKernelGGL((k_boundary_reg<T, TR, N, NF>), dim3(2 * nrhs), dim3(face_threads<N, NF>()), 0, c->stream, c->g.nz, \
+                     x, y, rout, sigtab<T>(c), e_rhs, active, part, (int)PQ_SLOTS, (int)PQ_BOUNDARY)
   switch (c->g.nf) {
     case 1: IOBM_BREG(1); break;
     case 2: IOBM_BREG(2); break;
@@ -1942,8 +1968,11 @@ static hipError_t launch_boundary(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx
       case 8: launch_boundary_reg<T, TR, 8>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
       case 12: launch_boundary_reg<T, TR, 12>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
       case 16: launch_boundary_reg<T, TR, 16>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
+      case 20: launch_boundary_reg<T, TR, 20>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
       case 24: launch_boundary_reg<T, TR, 24>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
       case 32: launch_boundary_reg<T, TR, 32>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
+      case 36: launch_boundary_reg<T, TR, 36>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
+      case 40: launch_boundary_reg<T, TR, 40>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
       case 48: launch_boundary_reg<T, TR, 48>(c, x, y, rout, nrhs, e_rhs, modes, active, part); break;
       default: reg = false;
     }
@@ -1951,9 +1980,16 @@ static hipError_t launch_boundary(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx
   if (!reg) {
     const size_t twb = (size_t)(c->g.nx + c->g.ny) * sizeof(cplx<T>);
     const int tw_lds = sh + twb + 1024 <= 160 * 1024;  // (1 KiB: the kernel's static arrays)
-    hipLaunchKernelGGL((k_boundary<T, TR>), dim3(2 * nrhs), dim3(fft_threads(c->g.nxy)), sh + (tw_lds ? twb : 0),
-                       c->stream, c->plan, c->g.nz, c->g.nf, x, y, rout, sigtab<T>(c), e_rhs, twx<T>(c), twy<T>(c),
-                       active, part, (int)PQ_SLOTS, (int)PQ_BOUNDARY, tw_lds);
+#define IOBM_BLDS(NF)                                                                                             \
+  hipLaunchKernelGGL((k_boundary<T, TR, NF>), dim3(2 * nrhs), dim3(fft_threads(c->g.nxy)), sh + (tw_lds ? twb : 0), \
+                     c->stream, c->plan, c->g.nz, x, y, rout, sigtab<T>(c), e_rhs, twx<T>(c), twy<T>(c), active,     \
+                     part, (int)PQ_SLOTS, (int)PQ_BOUNDARY, tw_lds)
+    switch (c->g.nf) {
+      case 1: IOBM_BLDS(1); break;
+      case 2: IOBM_BLDS(2); break;
+      default: IOBM_BLDS(3); break;
+    }
+#undef IOBM_BLDS
   }
   prof_stop(c, rec, (double)nrhs * 2 * c->g.nf * c->g.nxy * (2 * sizeof(cplx<T>) + sizeof(cplx<TR>)));
   return hipGetLastError();
