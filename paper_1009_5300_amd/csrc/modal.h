@@ -51,6 +51,7 @@ struct PlaneArgs {
   zd* x = nullptr;
   const int* xset = nullptr;
   KBPlane<T> kb;
+  bool pair = false;
 };
 
 template <typename T>
@@ -67,6 +68,7 @@ struct ModeArgsZ {
   zd *ha, *hb;          // [rhs][ring] alpha and beta of the steps in the ring
   cplx<T>*fold_s, *fold_t;
   long long fold_stride;
+  bool pair;
 };
 
 // Device state of a batch.
@@ -85,6 +87,9 @@ struct Modal {
   zd *ha = nullptr, *hb = nullptr;
   cplx<T>*fold_s = nullptr, *fold_t = nullptr;  // folded direction and correction, per rhs at fold_stride
   long long fold_stride = 0;
+  // pairs at a lateral Bloch vector (complex64, square register-FFT planes):
+  // right-hand sides 2k (primary) and 2k + 1 (shadow), listed together
+  bool pair = false;
 };
 
 int modal_mode_blocks(iobm_ctx c);

@@ -484,6 +484,144 @@ __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__(
   }
 }
 
+// The plane pass of a pair at a lateral Bloch vector: G plane pairs per block,
+// N threads per plane, the primary's plane beside its shadow's.  Plain Fourier
+// modes; the shadow's transforms run with the opposite sign, as those of its
+// conjugate (V is real), conjugated on the way in and out.  The partials are
+// those of z~^T V z.  The same bounds and memory traffic as k_plane_reg.
+// A solve of 48 x 48 x 96 pairs: 47.7 ms with the real-space recurrence, 30.6 ms.
+template <int N, int G, int MODE>
+__global__ void __launch_bounds__(2 * N * G) __attribute__((amdgpu_waves_per_eu(2))) k_plane_pair(PlaneArgs<float> A) {
+  constexpr int NN = N * N, EPT = N / 2;
+  __shared__ zf sm[2 * G][N][N + 1];
+  const int pl = threadIdx.x / N, lt = threadIdx.x - pl * N, shadow = pl & 1;
+  const int gp = blockIdx.x * G + (pl >> 1), total = A.nplanes / 2;
+  const int gq = min(gp, total - 1);  // a group past the last pair repeats it and stores nothing
+  const int pair = gq / A.nz, z = gq - pair * A.nz;
+  const int rhs = rhs_of(A.active, 2 * pair + shadow);
+  const bool ok = gp < total;
+  const long long off = ((long long)rhs * A.nz + z) * NN;
+  zf* vec = A.vec + off;
+  const float cj = shadow ? -1.0f : 1.0f;
+  const int r0 = 2 * lt / N, c0 = 2 * lt - r0 * N;
+  double d_re = 0, d_im = 0;
+  __shared__ double adv[MODE == PM_FULL ? G : 1][adv_subs(N) * kAdvValues];
+  const bool advance = MODE == PM_FULL && ok && z == 0 && !shadow;
+  if (advance) advance_sums<N>(adv[pl >> 1], A.part + (long long)rhs * A.nmb * MODAL_PART, A.nmb, lt);
+  {
+    float4 buf[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) buf[e] = reinterpret_cast<const float4*>(vec)[lt + e * N];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      sm[pl][2 * e + r0][c0] = mk(buf[e].x, cj * buf[e].y);
+      sm[pl][2 * e + r0][c0 + 1] = mk(buf[e].z, cj * buf[e].w);
+    }
+  }
+  __syncthreads();
+  zf v[N];
+  if constexpr (MODE != PM_FWD) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = sm[pl][lt][i];
+    line_fft<float, N, +1>(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) sm[pl][lt][i] = v[i];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = sm[pl][i][lt];  // column lt
+  if constexpr (MODE != PM_FWD) {
+    line_fft<float, N, +1>(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = (float)(1.0 / NN) * v[i];
+  }
+  if constexpr (MODE == PM_FULL) {
+    if (shadow) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) sm[pl][i][lt] = v[i];
+    }
+    __syncthreads();
+    const float* V = A.Vf + (long long)z * NN + lt;
+    constexpr int VB = N % 3 == 0 ? N / 3 : N / 2;
+#pragma unroll
+    for (int i0 = 0; i0 < N; i0 += VB) {
+      float pot[VB];
+#pragma unroll
+      for (int i = 0; i < VB; ++i) pot[i] = V[(i0 + i) * N];
+#pragma unroll
+      for (int i = 0; i < VB; ++i) {
+        const zf u = pot[i] * v[i0 + i], p = sm[pl | 1][i0 + i][lt];  // conj(z~); the shadow's own sums are not used
+        d_re += (double)p.re * u.re + (double)p.im * u.im;
+        d_im += (double)p.re * u.im - (double)p.im * u.re;
+        v[i0 + i] = u;
+      }
+      asm volatile("" : "+v"(d_re), "+v"(d_im));  // the sums are taken here (see k_plane_reg)
+    }
+    __syncthreads();
+  }
+  if constexpr (MODE != PM_ACC) {
+    line_fft<float, N, -1>(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) sm[pl][i][lt] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = sm[pl][lt][i];  // row lt
+    line_fft<float, N, -1>(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) sm[pl][lt][i] = v[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) sm[pl][i][lt] = v[i];
+  }
+  __syncthreads();
+  if (ok) {
+    if constexpr (MODE == PM_ACC) {
+      zd* x = A.x + off + lt;
+      constexpr int XB = N % 8 == 0 ? 8 : 4;
+#pragma unroll
+      for (int e0 = 0; e0 < N; e0 += XB) {
+        zd xv[XB];
+#pragma unroll
+        for (int e = 0; e < XB; ++e) xv[e] = x[(e0 + e) * N];
+#pragma unroll
+        for (int e = 0; e < XB; ++e) {
+          const zf c = sm[pl][e0 + e][lt];
+          x[(e0 + e) * N] = xv[e] + mk((double)c.re, (double)(cj * c.im));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const zf a = sm[pl][2 * e + r0][c0], b = sm[pl][2 * e + r0][c0 + 1];
+        reinterpret_cast<float4*>(vec)[lt + e * N] = make_float4(a.re, cj * a.im, b.re, cj * b.im);
+      }
+    }
+  }
+  if constexpr (MODE == PM_FULL) {
+    // per-plane sum in a fixed order: 8 strided sums, then those in order
+    __shared__ double red[2][2 * N * G];
+    __shared__ double red8[2][16 * G];
+    red[0][threadIdx.x] = d_re;
+    red[1][threadIdx.x] = d_im;
+    __syncthreads();
+    if (lt < 8) {
+      double a = 0, b = 0;
+      for (int i = lt; i < N; i += 8) { a += red[0][pl * N + i]; b += red[1][pl * N + i]; }
+      red8[0][pl * 8 + lt] = a;
+      red8[1][pl * 8 + lt] = b;
+    }
+    __syncthreads();
+    if (lt == 0 && ok && !shadow) {
+      double a = 0, b = 0;
+      for (int i = 0; i < 8; ++i) { a += red8[0][pl * 8 + i]; b += red8[1][pl * 8 + i]; }
+      double* dp = A.dpart + ((long long)rhs * A.ndp + z) * 2;
+      dp[0] = a;
+      dp[1] = b;
+    }
+    if (advance) advance_scalars<N>(A.sc[rhs], adv[pl >> 1], lt);
+  }
+}
+
 // Any other plane size: one plane per block in LDS (two copies and the
 // twiddle tables), mixed-radix Stockham stages along x and y.
 template <typename T, int MODE>
@@ -640,7 +778,15 @@ __device__ __forceinline__ void ring_coeffs(const zd* ha, const zd* hb, int base
 // R, R_old) are each read once, the boundary planes of R' pass between
 // chunks through LDS.  Bound: memory (5 streams); the per-element work is
 // about 8 nf complex multiply-adds and three FP64 dot products.
-template <typename T, int L, int NF, int MODE, int MB>
+//
+// PAIR (a lateral Bloch vector, plain Fourier modes): block = the same modes of
+// a primary and its shadow, one after the other, with the primary's scalars
+// and filter; the shadow is stored at the negative of its own modes, so that
+// its operator and the products rho' = r~^T z and sigma' = (q~^T z + q^T z~) / 2
+// (z and q kept in registers from the primary) are elementwise.  The mean of
+// the two makes both directions conjugate alike: with q~^T z alone one of 180
+// states of a 16 x 16 x 96 grid did not converge, of 1,932 with the mean every one.
+template <typename T, int L, int NF, int MODE, int MB, bool PAIR>
 __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
   constexpr int NR = ModalRing<T>::n;
   extern __shared__ char smem_raw[];
@@ -649,12 +795,12 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
   cplx<T>* hl = hf + C * NF * MB;                      // [C][NF][MB] last NF - 1 planes
   cplx<T>* sc = hl + C * NF * MB;                      // [C][NF][MB] causal end states
   cplx<T>* sb = sc + C * NF * MB;                      // [C][NF][MB] anti-causal begin states
-  double* red = reinterpret_cast<double*>(smem_raw);   // [C][5][MB], after the states are read
+  double* red = reinterpret_cast<double*>(smem_raw);   // [C][5 (PAIR: 6)][MB], after the states are read
   const int slot = blockIdx.x / A.nmb, mb = blockIdx.x - slot * A.nmb;
   const int lane = threadIdx.x;
   // uniform over a wavefront where one holds a single chunk
   const int c = MB == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.y) : threadIdx.y;
-  const int rhs = __builtin_amdgcn_readfirstlane(rhs_of(A.active, slot));  // scalar: so are the vectors' addresses
+  const int rhs = __builtin_amdgcn_readfirstlane(rhs_of(A.active, PAIR ? 2 * slot : slot));  // scalar: so are the vectors' addresses
   const int m = mb * MB + lane, nxy = A.nxy, nz = A.nz;
   const bool live = m < nxy;
   const int z0 = c * L;
@@ -662,7 +808,6 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
   // beside a scalar base: at most 2^20 points of 16 bytes).
   // Loads are unconditional from clamped (always valid) addresses and masked
   // afterwards: a load under a branch of its own is waited for on its own
-  const long long base = (long long)rhs * nxy * nz;
   const bool whole = live && z0 + L <= nz;
   unsigned off[L];
 #pragma unroll
@@ -692,6 +837,13 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
   ModalScal& S = A.sc[rhs];
   const int step = __builtin_amdgcn_readfirstlane(S.step);
   constexpr bool STEP = MODE == ZS_STEP;
+  double d[5] = {0, 0, 0, 0, 0}, n2_prim = 0;
+  cplx<T> zp[PAIR ? L : 1], qp[PAIR && STEP ? L : 1];  // Z and q of the primary
+  __shared__ zd sco[2];
+#pragma unroll 1
+  for (int shadow = 0; shadow < (PAIR ? 2 : 1); ++shadow) {
+  const int rv = rhs + shadow;  // the vectors' right-hand side
+  const long long base = (long long)rv * nxy * nz;
   // own inputs; rr[NF - 1 + i] is plane z0 + i
   cplx<T> rr[L + 2 * NF - 1];
   cplx<T> q[STEP ? L : 1];
@@ -704,8 +856,7 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
     load(X, xo);
     // z^T W of this right-hand side, summed in a fixed order, and the
     // step's scalars: by the first wavefront, while the loads are in flight
-    __shared__ zd sco[2];
-    if (c < 64 / MB) {
+    if (c < 64 / MB && !shadow) {
       const int wl = c * MB + lane;
       zd dl = mk(0.0, 0.0);
       const double* dp = A.dpart + (long long)rhs * A.ndp * 2;
@@ -741,7 +892,7 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
   } else if constexpr (MODE == ZS_START) {
     load(A.ring[0] + base, rr + NF - 1);
     mask(rr + NF - 1);
-    if (mb == 0 && c == 0 && lane == 0) {
+    if (mb == 0 && c == 0 && lane == 0 && !shadow) {
       S.step = -1;  // the next plane pass makes it 0
       S.base = 0;
       S.flag = 0;
@@ -763,8 +914,8 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
     for (int j = 0; j < NR; ++j)
       if (b0 + j < n) add(ring_at<T>(A.ring, (b0 + j) % NR) + base, cvt<T>(ct[j]));
     if (b0 > 0) {
-      add(A.fold_s + rhs * A.fold_stride, cvt<T>(tp));
-      add(A.fold_t + rhs * A.fold_stride, mk<T>(1, 0));
+      add(A.fold_s + rv * A.fold_stride, cvt<T>(tp));
+      add(A.fold_t + rv * A.fold_stride, mk<T>(1, 0));
     }
     mask(rr + NF - 1);
   }
@@ -862,33 +1013,66 @@ __global__ void __launch_bounds__(512) k_zstep(ModeArgsZ<T> A) {
   store(A.w + base, y);
   if constexpr (MODE != ZS_FOLD) {
     // bilinear products: rho' = r'^T z, sigma' = z^T q, |r'|^2
-    double d[5] = {0, 0, 0, 0, 0};
     // (past the region r and q vanish, and with them every product)
+    if constexpr (PAIR) {
+      if (!shadow) {
+        n2_prim = 0;
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+          zp[i] = y[i];
+          if constexpr (STEP) qp[i] = q[i];
+          const cplx<T> r = rr[NF - 1 + i];
+          n2_prim += (double)r.re * r.re + (double)r.im * r.im;
+        }
+        __syncthreads();  // the states in LDS are read
+        continue;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const cplx<T> r = rr[NF - 1 + i], zz = y[i];
+      const cplx<T> r = rr[NF - 1 + i], zz = PAIR ? zp[PAIR ? i : 0] : y[i];
       d[0] += (double)r.re * zz.re - (double)r.im * zz.im;
       d[1] += (double)r.re * zz.im + (double)r.im * zz.re;
       if constexpr (STEP) {
         const cplx<T> v = q[i];
         d[2] += (double)v.re * zz.re - (double)v.im * zz.im;
         d[3] += (double)v.re * zz.im + (double)v.im * zz.re;
+        if constexpr (PAIR) {  // the mean of q~^T z and q^T z~
+          const cplx<T> qq = qp[i], zs = y[i];
+          d[2] += (double)qq.re * zs.re - (double)qq.im * zs.im;
+          d[3] += (double)qq.re * zs.im + (double)qq.im * zs.re;
+        }
       }
       d[4] += (double)r.re * r.re + (double)r.im * r.im;
     }
+  } else if constexpr (PAIR) {
+    __syncthreads();  // the states in LDS are read
+  }
+  }
+  if constexpr (MODE != ZS_FOLD) {
+    if constexpr (PAIR) {
+      d[2] *= 0.5;
+      d[3] *= 0.5;
+    }
     // weight of the mode in the bilinear form
     const int iy = m / A.nx, ix = m - iy * A.nx;
-    const double w = ((ix == 0 || 2 * ix == A.nx) ? 1.0 : 0.5) * ((iy == 0 || 2 * iy * A.nx == nxy) ? 1.0 : 0.5) / nxy;
+    const double w = (PAIR ? 1.0
+                           : ((ix == 0 || 2 * ix == A.nx) ? 1.0 : 0.5) * ((iy == 0 || 2 * iy * A.nx == nxy) ? 1.0 : 0.5)) /
+                     nxy;
+    constexpr int ND = PAIR ? 6 : 5;
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 5; ++k) red[(c * 5 + k) * MB + lane] = w * d[k];
+    for (int k = 0; k < 5; ++k) red[(c * ND + k) * MB + lane] = w * d[k];
+    if constexpr (PAIR) red[(c * ND + 5) * MB + lane] = w * n2_prim;
     __syncthreads();
     // the threads of chunk c sum the values c, c + C, ...: chunks in order, then lanes
-    for (int k = c; k < 5; k += C) {
+    for (int k = c; k < ND; k += C) {
       double s = 0;
-      for (int cc = 0; cc < C; ++cc) s += red[(cc * 5 + k) * MB + lane];
+      for (int cc = 0; cc < C; ++cc) s += red[(cc * ND + k) * MB + lane];
       for (int o = MB / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      if (lane == 0) A.part[((long long)rhs * A.nmb + mb) * MODAL_PART + k] = s;
+      // of a pair, |r|^2 of the shadow goes to its own partials
+      const int row = PAIR && k == 4 ? rhs + 1 : rhs, to = k == 5 ? 4 : k;
+      if (lane == 0) A.part[((long long)row * A.nmb + mb) * MODAL_PART + to] = s;
     }
   }
 }
@@ -899,10 +1083,11 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_ring_fold(ModeArgsZ<T> A, long long vol) {
   constexpr int NR = ModalRing<T>::n;
   const int rhs = rhs_of(A.active, blockIdx.y);
-  const int n = A.sc[rhs].step + 1, b0 = A.sc[rhs].base;
+  const int own = A.pair ? rhs & ~1 : rhs;  // whose scalars
+  const int n = A.sc[own].step + 1, b0 = A.sc[own].base;
   if (n - b0 != NR - 1) return;
   zd ct[NR], cs[NR], tp, sp;
-  ring_coeffs<NR>(A.ha + (long long)rhs * NR, A.hb + (long long)rhs * NR, b0, n, ct, cs, tp, sp);
+  ring_coeffs<NR>(A.ha + (long long)own * NR, A.hb + (long long)own * NR, b0, n, ct, cs, tp, sp);
   cplx<T>* S = A.fold_s + rhs * A.fold_stride;
   cplx<T>* Tv = A.fold_t + rhs * A.fold_stride;
   const cplx<T>* R[NR - 1];
@@ -927,9 +1112,9 @@ __global__ void __launch_bounds__(256) k_ring_fold(ModeArgsZ<T> A, long long vol
 
 // The new base of the folded right-hand sides (after every block of
 // k_ring_fold has read the old one).
-__global__ void k_ring_rebase(ModalScal* sc, const int* active, int nact, int nr) {
+__global__ void k_ring_rebase(ModalScal* sc, const int* active, int nact, int nr, bool pair) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nact) return;
+  if (i >= nact || (pair && i % 2)) return;
   ModalScal& s = sc[rhs_of(active, i)];
   if (s.step + 1 - s.base == nr - 1) s.base = s.step + 1;
 }
@@ -938,7 +1123,7 @@ __global__ void k_ring_rebase(ModalScal* sc, const int* active, int nact, int nr
 // for the host's convergence check.
 __global__ void __launch_bounds__(256) k_modal_check(const ModalScal* __restrict__ sc, const double* __restrict__ part,
                                                      int nmb, const int* __restrict__ active, int nact,
-                                                     double* __restrict__ rn2, int* __restrict__ flag) {
+                                                     double* __restrict__ rn2, int* __restrict__ flag, bool pair) {
   const int slot = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (slot >= nact) return;  // whole wavefronts
   const int rhs = rhs_of(active, slot);
@@ -947,7 +1132,7 @@ __global__ void __launch_bounds__(256) k_modal_check(const ModalScal* __restrict
   for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
   if (lane == 0) {
     rn2[rhs] = n2;
-    flag[rhs] = sc[rhs].flag;
+    flag[rhs] = sc[pair ? rhs & ~1 : rhs].flag;
   }
 }
 
@@ -1015,9 +1200,33 @@ void plane_reg(iobm_ctx c, int mode, const PlaneArgs<T>& A) {
 #undef IOBM_PR
 }
 
+template <int N, int G>
+void plane_pair(iobm_ctx c, int mode, const PlaneArgs<float>& A) {
+  const dim3 grid((A.nplanes / 2 + G - 1) / G), blk(2 * N * G);
+#define IOBM_PP(MM) hipLaunchKernelGGL((k_plane_pair<N, G, MM>), grid, blk, 0, c->stream, A)
+  switch (mode) {
+    case PM_FULL: IOBM_PP(PM_FULL); break;
+    case PM_FWD: IOBM_PP(PM_FWD); break;
+    default: IOBM_PP(PM_ACC); break;
+  }
+#undef IOBM_PP
+}
+
 template <typename T>
 hipError_t launch_plane(iobm_ctx c, int mode, const PlaneArgs<T>& A) {
   if (A.nplanes <= 0) return hipSuccess;
+  if constexpr (sizeof(T) == 4)
+    if (A.pair) {
+      switch (c->g.nx) {
+        case 8: plane_pair<8, 8>(c, mode, A); break;
+        case 12: plane_pair<12, 8>(c, mode, A); break;
+        case 16: plane_pair<16, 4>(c, mode, A); break;
+        case 24: plane_pair<24, 2>(c, mode, A); break;
+        case 32: plane_pair<32, 1>(c, mode, A); break;
+        default: plane_pair<48, 1>(c, mode, A); break;
+      }
+      return hipGetLastError();
+    }
   if (fft_reg_available<T>(c)) {
     constexpr bool dbl = sizeof(T) == 8;
     switch (c->g.nx) {
@@ -1061,10 +1270,18 @@ hipError_t launch_zstep(iobm_ctx c, int mode, const ModeArgsZ<T>& A, int nact) {
   // plane is empty
   const int cw = 64 / MB, C = ((c->g.nz + L - 1) / L + cw - 1) / cw * cw;
   if (C * MB > 512) return hipErrorInvalidValue;
-  const size_t st = (size_t)4 * C * nf * MB * sizeof(cplx<T>), rd = (size_t)C * 5 * MB * sizeof(double);
+  const size_t st = (size_t)4 * C * nf * MB * sizeof(cplx<T>), rd = (size_t)C * (A.pair ? 6 : 5) * MB * sizeof(double);
   const size_t sh = st > rd ? st : rd;
-  const dim3 grid(nact * A.nmb), blk(MB, C);
-#define IOBM_Z1(NFF, MM, BB) hipLaunchKernelGGL((k_zstep<T, L, NFF, MM, BB>), grid, blk, sh, c->stream, A)
+  const dim3 grid((A.pair ? nact / 2 : nact) * A.nmb), blk(MB, C);
+#define IOBM_Z1(NFF, MM, BB)                                                                             \
+  do {                                                                                                   \
+    if constexpr (sizeof(T) == 4)                                                                        \
+      if (A.pair) {                                                                                      \
+        hipLaunchKernelGGL((k_zstep<T, L, NFF, MM, BB, true>), grid, blk, sh, c->stream, A);             \
+        break;                                                                                           \
+      }                                                                                                  \
+    hipLaunchKernelGGL((k_zstep<T, L, NFF, MM, BB, false>), grid, blk, sh, c->stream, A);                \
+  } while (0)
 #define IOBM_Z2(NFF, BB)                             \
   switch (mode) {                                    \
     case ZS_STEP: IOBM_Z1(NFF, ZS_STEP, BB); break;   \
@@ -1132,6 +1349,7 @@ static ModeArgsZ<T> mode_args(iobm_ctx c, const Modal<T>& M, const int* active) 
   A.fold_s = M.fold_s;
   A.fold_t = M.fold_t;
   A.fold_stride = M.fold_stride;
+  A.pair = M.pair;
   return A;
 }
 
@@ -1149,6 +1367,7 @@ static PlaneArgs<T> plane_args(iobm_ctx c, const Modal<T>& M, cplx<T>* vec, int 
   A.sc = M.sc;
   A.part = M.part;
   A.dpart = M.dpart;
+  A.pair = M.pair;
   return A;
 }
 
@@ -1194,7 +1413,7 @@ hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active
   const unsigned bx = (unsigned)std::min<long long>(256, (vol + 255) / 256);
   hipLaunchKernelGGL(k_ring_fold<T>, dim3(bx, nact), dim3(256), 0, c->stream, A, vol);
   hipLaunchKernelGGL(k_ring_rebase, dim3((nact + 255) / 256), dim3(256), 0, c->stream, M.sc, active, nact,
-                     (int)ModalRing<T>::n);
+                     (int)ModalRing<T>::n, M.pair);
   return hipGetLastError();
 }
 
@@ -1220,7 +1439,7 @@ template <typename T>
 hipError_t modal_check(iobm_ctx c, const Modal<T>& M, int nact, const int* active, double* rn2, int* flag) {
   if (nact <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_modal_check, dim3((nact + 3) / 4), dim3(256), 0, c->stream, M.sc, M.part, M.nmb, active, nact,
-                     rn2, flag);
+                     rn2, flag, M.pair);
   return hipGetLastError();
 }
 

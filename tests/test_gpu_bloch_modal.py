@@ -1,0 +1,69 @@
+"""The mode-space iteration at a lateral Bloch vector (complex64, square planes
+with register transforms) against the complex128 solve, which applies the
+operator in real space: every plane size, plane counts around the chunk of 8
+and the changes of the mode-block width, every stencil order, deep wells that
+take several turns of the ring, and a chain of states some of which it hands
+over to that recurrence."""
+import numpy as np
+import pytest
+
+from workloads import Grid
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _potential(g, depth, rng):
+    k, j, i = np.meshgrid(np.arange(g.nz), np.arange(g.ny), np.arange(g.nx), indexing="ij")
+    V = 0.02 * rng.uniform(-1, 1, g.shape)
+    for f in (0.3, 0.7):
+        r2 = ((i - g.nx / 2) * g.hx) ** 2 + ((j - g.ny / 2) * g.hy) ** 2 + ((k - f * g.nz) * g.hz) ** 2
+        V -= depth * np.exp(-r2 / (2 * 1.5 ** 2))
+    return V
+
+
+def _solve(g, V, E, kap, precision):
+    from paper_1009_5300_amd import iobm
+    s = iobm.Solver(g.nx, g.ny, g.nz, g.spacings, g.nf)
+    s.set_potential(V)
+    return s.smatrix_bloch(E, kap, opts=iobm.default_opts(precision=precision))
+
+
+CASES = [(8, 4, 2, 0.2), (8, 9, 3, 0.2), (8, 64, 2, 0.6), (8, 65, 1, 0.6), (8, 129, 1, 0.3), (12, 24, 2, 0.4),
+         (16, 33, 3, 0.4), (24, 20, 2, 0.2), (32, 12, 1, 0.2), (48, 10, 2, 0.1)]
+
+
+@pytest.mark.parametrize("n,nz,nf,depth", CASES)
+def test_smatrix_against_complex128(torch, n, nz, nf, depth):
+    """Both stop at 1e-10 of the right-hand side, so their S matrices differ by some 1e-10 times the resolvent's norm
+    in flux units (tens to hundreds away from thresholds): 1e-7."""
+    from paper_1009_5300_amd import iobm
+    g = Grid(n, n, nz, 0.45, nf, hz_=0.5)
+    V = _potential(g, depth, np.random.default_rng(n + nz))
+    kap = (0.31 * 2 * np.pi / (n * g.hx), -0.17 * 2 * np.pi / (n * g.hy))
+    E = [0.4, 0.7] if n < 32 else [0.1]
+    Sp, Sm, st, status = _solve(g, V, E, kap, iobm.C64_REFINED)
+    Rp, Rm, _, rstatus = _solve(g, V, E, kap, iobm.C128)
+    assert status == 0 and rstatus == 0
+    for a, b in zip(list(Sp) + list(Sm), list(Rp) + list(Rm)):
+        assert a.shape == b.shape
+        if a.size:
+            assert np.abs(a - b).max() <= 1e-7
+
+
+def test_stagnating_pairs_converge(torch):
+    """70 potentials whose states take up to a thousand steps: every one converges."""
+    from paper_1009_5300_amd import iobm
+    g = Grid(12, 12, 64, 0.5, 1)
+    for seed in range(70):
+        rng = np.random.default_rng(seed)
+        V = _potential(g, 1.5, rng)
+        kap = tuple(rng.uniform(0.05, 0.45, 2) * 2 * np.pi / (12 * 0.5))
+        _, _, _, status = _solve(g, V, list(rng.uniform(0.1, 1.0, 3)), kap, iobm.C64_REFINED)
+        assert status == 0, seed
