@@ -34,8 +34,10 @@ HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
 # the git blob ids of the sources it was measured on: the kernels, and the
 # solver driver, whose iteration schedule sets the sizes of the launches
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.txt")
-KERNEL_SOURCES = ["paper_1009_5300_amd/csrc/ops.hip", "paper_1009_5300_amd/csrc/common.h",
-                  "paper_1009_5300_amd/csrc/internal.h", "paper_1009_5300_amd/csrc/api.hip"]
+KERNEL_SOURCES = ["paper_1009_5300_amd/csrc/ops.hip", "paper_1009_5300_amd/csrc/modal.hip",
+                  "paper_1009_5300_amd/csrc/modal.h", "paper_1009_5300_amd/csrc/fftreg.h",
+                  "paper_1009_5300_amd/csrc/common.h", "paper_1009_5300_amd/csrc/internal.h",
+                  "paper_1009_5300_amd/csrc/api.hip"]
 
 
 def _blob_id(path):

@@ -352,9 +352,9 @@ iobm_status iobm_grad_transmission(iobm_ctx ctx, const iobm_solve_opts* opts, in
  *                      compute unit has blocks)
  *   zfilter_chunk:     lateral-Fourier preconditioner, 8, 16 or 32 planes per
  *                      chunk of the z recursion (at most 8 chunks) in
- *                      iobm_precondition, block COCG and the solve at a
- *                      Bloch vector; the mode-space iteration of the other
- *                      solves takes 8 planes always
+ *                      iobm_precondition, block COCG and the complex128
+ *                      solve at a Bloch vector; the mode-space iteration of
+ *                      the other solves takes 8 planes always
  *   plane_fft:         1 = in-register plane transforms (square planes of 8,
  *                      12, 16, 24, 32 or 48 points), 2 = LDS Stockham stages
  *   rz_pass:           lateral-Fourier preconditioner with the in-register

@@ -564,7 +564,7 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
     HIPCHK(hipMemsetAsync(beta, 0x3F, nb * sizeof(zd), ctx->stream));
     HIPCHK(hipMemsetAsync(alpha, 0x3F, nb * sizeof(zd), ctx->stream));  // d += alpha * 0 leaves d = 0
     ApplyFuse<T> TF{r, pa, beta, pb, part_pq, alpha, d, dlive};
-    autotune<T>(ctx, r, q, nullptr, nact, E_d, e_d, modes, act_d, &TF);
+    autotune<T>(ctx, q, nact, E_d, act_d, TF);
     HIPCHK(hipMemsetAsync(part_pq, 0, (size_t)nb * PQ_SLOTS * sizeof(Partial), ctx->stream));
   }
   restart(nact, act_d);

@@ -290,13 +290,10 @@ int precond_slots(iobm_ctx c, int precond);
 template <typename T>
 hipError_t launch_kb_apply(iobm_ctx c, const cplx<T>* x, cplx<T>* y, int nrhs, Partial* pq_part,
                            const int* active);
-// Times the admissible stencil shapes (on the fused operator when `fuse` is
-// given; its buffers are overwritten) and z-filter chunk lengths once per
-// context and precision, unless a shape is pinned.
+// Times the admissible stencil shapes on the fused operator (its buffers and y
+// are overwritten) once per context and precision, unless a shape is pinned.
 template <typename T>
-void autotune(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx<T>* scratch, int nrhs, const double* E_rhs,
-              const int* e_rhs, const ModeData* modes, const int* active, const ApplyFuse<T>* fuse = nullptr,
-              Partial* rz_part = nullptr);
+void autotune(iobm_ctx c, cplx<T>* y, int nrhs, const double* E_rhs, const int* active, const ApplyFuse<T>& fuse);
 size_t kb_proj_bytes(iobm_ctx c, int nrhs);
 // Launch-shape rules (ops.hip): whether a pinned shape is admissible for
 // this grid, and the shape in effect (pinned, tuned or the default rule).

@@ -489,7 +489,7 @@ __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__(
 // modes; the shadow's transforms run with the opposite sign, as those of its
 // conjugate (V is real), conjugated on the way in and out.  The partials are
 // those of z~^T V z.  The same bounds and memory traffic as k_plane_reg.
-// A solve of 48 x 48 x 96 pairs: 47.7 ms with the real-space recurrence, 30.6 ms.
+// A solve of 48 x 48 x 128 pairs: 47.7 ms with the real-space recurrence, 30.6 ms.
 template <int N, int G, int MODE>
 __global__ void __launch_bounds__(2 * N * G) __attribute__((amdgpu_waves_per_eu(2))) k_plane_pair(PlaneArgs<float> A) {
   constexpr int NN = N * N, EPT = N / 2;

@@ -2292,14 +2292,10 @@ hipError_t launch_precond_fft(iobm_ctx c, const cplx<T>* r, cplx<T>* z, cplx<T>*
 }
 
 // Autotuner: time every admissible (points per thread, planes per block)
-// shape of the 2.5D stencil and every z-filter chunk length once on the
-// caller's own batch (x -> y, y is scratch), keep the fastest per precision.
-// With rz_part (nrhs x nz partials), the z filter is timed as the
-// preconditioner will run it: with the r^T z partials where it takes them.
+// shape of the 2.5D stencil on the caller's own batch and fused operator
+// (its buffers and y are overwritten), keep the fastest per precision.
 template <typename T>
-void autotune(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx<T>* scratch, int nrhs, const double* E_rhs,
-              const int* e_rhs, const ModeData* modes, const int* active, const ApplyFuse<T>* fuse,
-              Partial* rz_part) {
+void autotune(iobm_ctx c, cplx<T>* y, int nrhs, const double* E_rhs, const int* active, const ApplyFuse<T>& fuse) {
   bool& done = c->tuned[prec_index<T>()];
   if (done || nrhs <= 0) return;
   done = true;
@@ -2326,49 +2322,21 @@ void autotune(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx<T>* scratch, int nr
         if (!a25_ppt_ok(c, ppt)) continue;
         if (zc > c->g.nz && zc != 16) continue;
         float t = timed([&] {
-          if (fuse)
-            launch_apply25_shape<T>(c, ppt, zc,
-                                    OpFuseP<T>{fuse->z, fuse->pold, fuse->beta, fuse->pnew, y, fuse->part,
-                                               fuse->alpha, fuse->d, fuse->dlive},
-                                    nrhs, E_rhs, active);
-          else
-            launch_apply25_shape<T>(c, ppt, zc, OpPlain<T>{x, y}, nrhs, E_rhs, active);
+          launch_apply25_shape<T>(c, ppt, zc,
+                                  OpFuseP<T>{fuse.z, fuse.pold, fuse.beta, fuse.pnew, y, fuse.part, fuse.alpha,
+                                             fuse.d, fuse.dlive},
+                                  nrhs, E_rhs, active);
         });
         if (t < best) { best = t; bp = ppt; bz = zc; }
       }
     if (bp > 0) { sh.stencil = 1; sh.points_per_thread = bp; sh.planes_per_block = bz; }
   }
-  if (scratch) {
-    // the z filter's chunk length and, where the z filter can take the r^T z
-    // partials, which pass takes them: each composition is timed with the
-    // inverse transform that follows the filter (plain after the filter's
-    // dot, with the dot from R otherwise)
-    const bool try_dot = rz_part != nullptr && zfilter_dot_ok<T>(c);
-    float best = 1e30f;
-    int bl = 0, bd = 0;
-    for (int dot = 0; dot <= (try_dot ? 1 : 0); ++dot)
-      for (int L : {8, 16, 32}) {
-        if ((c->g.nz + L - 1) / L > 8) continue;
-        float t = timed([&] {
-          (void)launch_zfilter<T>(c, L, scratch, y, nrhs, e_rhs, modes, active, dot ? rz_part : nullptr);
-          if (try_dot && dot)
-            (void)launch_fft_planes<T>(c, y, y, +1, 1.0 / c->g.nxy, nrhs, active);
-          else if (try_dot)
-            (void)launch_fft_planes<T>(c, y, y, +1, 1.0 / c->g.nxy, nrhs, active, nullptr, scratch, rz_part);
-        });
-        if (t < best) { best = t; bl = L; bd = dot; }
-      }
-    if (bl > 0) sh.zfilter_chunk = bl;
-    if (try_dot && bl > 0) sh.rz_pass = bd ? 1 : 2;
-  }
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
 }
 
-template void autotune<float>(iobm_ctx, const zf*, zf*, zf*, int, const double*, const int*, const ModeData*,
-                              const int*, const ApplyFuse<float>*, Partial*);
-template void autotune<double>(iobm_ctx, const zd*, zd*, zd*, int, const double*, const int*, const ModeData*,
-                               const int*, const ApplyFuse<double>*, Partial*);
+template void autotune<float>(iobm_ctx, zf*, int, const double*, const int*, const ApplyFuse<float>&);
+template void autotune<double>(iobm_ctx, zd*, int, const double*, const int*, const ApplyFuse<double>&);
 
 template hipError_t launch_apply<double>(iobm_ctx, const zd*, zd*, int, const double*, const int*,
                                          const ModeData*, const int*, const ApplyFuse<double>*);
