@@ -201,7 +201,9 @@ IOBM_HD void lagrange_row(const zd* r, int p, zd* L) {
 }
 
 // One mode of one energy.  The order is a template argument: with a run-time
-// order every small array is indexed at run time and lives in scratch memory.
+// order every small array is indexed at run time and lives in scratch memory
+// (46 to 110 us per table; now 8 us at 16 x 16, nf = 2, and 26 us at 24 x 24,
+// nf = 3, 32 energies, bound by the latency of one thread's chain).
 template <int nf>
 __device__ __forceinline__ void compute_mode(const ModeArgs& A, double E, int m, ModeData* out) {
   const double* c = A.c;
