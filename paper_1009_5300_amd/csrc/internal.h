@@ -278,6 +278,12 @@ hipError_t launch_rhs(iobm_ctx c, int nrhs, const int* e_rhs, const int* mode_rh
 hipError_t launch_readout(iobm_ctx c, int nrhs, int side, const zd* x, const ModeData* modes, const int* e_rhs,
                           zd* amp_near, zd* amp_far);
 int dot_blocks(iobm_ctx c);
+// Whether `bytes` of dynamic LDS, and up to 1 KiB of a kernel's static arrays,
+// fit a workgroup (gfx950: 160 KiB).  iobm_create admits every grid whose nf + 1
+// complex128 planes fit; the plane kernels hold two and, where this says so,
+// the twiddle tables beside them, which do not fit for 2 x 2040 to 2 x 2048
+// points in complex128 (with 128 projectors from 2 x 2016 on).
+inline bool lds_holds(size_t bytes) { return bytes + 1024 <= 160 * 1024; }
 // whether the plane transforms of this context run in registers (square planes
 // of the fixed list, unless the launch shape names the LDS path)
 template <typename T>

@@ -623,9 +623,9 @@ __global__ void __launch_bounds__(2 * N * G) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-// Any other plane size: one plane per block in LDS (two copies and the
-// twiddle tables), mixed-radix Stockham stages along x and y.
-template <typename T, int MODE>
+// Any other plane size: one plane per block in LDS (two copies and, with TW,
+// the twiddle tables: see lds_holds), mixed-radix Stockham stages along x and y.
+template <typename T, int MODE, bool TW>
 __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D plan, const cplx<T>* __restrict__ twx,
                                                    const cplx<T>* __restrict__ twy) {
   extern __shared__ char smem_raw[];
@@ -633,8 +633,8 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
   cplx<T>* a = reinterpret_cast<cplx<T>*>(smem_raw);
   cplx<T>* b = a + nxy;
   cplx<T>* tx = b + nxy;
-  cplx<T>* ty = tx + nx;
-  double* red = reinterpret_cast<double*>(ty + ny);  // [2][4]
+  cplx<T>* ty = tx + (TW ? nx : 0);
+  double* red = reinterpret_cast<double*>(ty + (TW ? ny : 0));  // [2][4]
   double* adv = red + 8;                             // [16][5]
   const int slot = blockIdx.x / A.nz, z = blockIdx.x - slot * A.nz;
   const int rhs = rhs_of(A.active, slot);
@@ -646,8 +646,14 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
   const bool advance = pm_sum(MODE) && z == 0;
   if (advance) advance_sums<256>(adv, A.part + (long long)rhs * A.nmb * MODAL_PART, A.nmb, threadIdx.x);
   const float inx = 1.0f / (float)nx;
-  for (int i = threadIdx.x; i < nx; i += blockDim.x) tx[i] = twx[i];
-  for (int i = threadIdx.x; i < ny; i += blockDim.x) ty[i] = twy[i];
+  if constexpr (TW) {
+    for (int i = threadIdx.x; i < nx; i += blockDim.x) tx[i] = twx[i];
+    for (int i = threadIdx.x; i < ny; i += blockDim.x) ty[i] = twy[i];
+  }
+  auto fft = [&](cplx<T>* in, cplx<T>* tmp, int sign) -> cplx<T>* {
+    if constexpr (TW) return fft2d_lds(in, tmp, plan, tx, ty, sign);
+    else return fft2d_lds(in, tmp, plan, twx, twy, sign);
+  };
   for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
     cplx<T> c = vec[p];
     if constexpr (MODE == PM_VFWD) {
@@ -677,7 +683,7 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
       b[p] = cs_f(j, ny, cs_f(i, nx, a[jp + i], a[jp + im]), cs_f(i, nx, a[jm + i], a[jm + im]));
     }
     __syncthreads();
-    src = fft2d_lds(b, a, plan, tx, ty, +1);
+    src = fft(b, a, +1);
     const T scale = (T)(0.25 / nxy);
     if constexpr (MODE == PM_ACC) {
       zd* x = A.x + off;
@@ -699,7 +705,7 @@ __global__ void __launch_bounds__(256) k_plane_lds(PlaneArgs<T> A, FFTPlan2D pla
     }
   }
   if constexpr (HAS_FWD) {
-    cplx<T>* f = fft2d_lds(src, src == a ? b : a, plan, tx, ty, -1);
+    cplx<T>* f = fft(src, src == a ? b : a, -1);
     for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
       const int j = small_quotient(p, inx), i = p - j * nx;
       const int jm = (j ? ny - j : 0) * nx, im = i ? nx - i : 0, jp = j * nx;
@@ -1246,10 +1252,18 @@ hipError_t launch_plane(iobm_ctx c, int mode, const PlaneArgs<T>& A) {
     }
     return hipGetLastError();
   }
-  const size_t sh = (2 * (size_t)c->g.nxy + c->g.nx + c->g.ny) * sizeof(cplx<T>) + (8 + 16 * kAdvValues) * sizeof(double) +
+  const size_t sh = 2 * (size_t)c->g.nxy * sizeof(cplx<T>) + (8 + 16 * kAdvValues) * sizeof(double) +
                     (mode == PM_VFWD ? A.kb.npad * sizeof(cplx<T>) : 0);
-#define IOBM_PL(MM) \
-  hipLaunchKernelGGL((k_plane_lds<T, MM>), dim3(A.nplanes), dim3(256), sh, c->stream, A, c->plan, twx_of<T>(c), twy_of<T>(c))
+  const size_t tables = (size_t)(c->g.nx + c->g.ny) * sizeof(cplx<T>);
+  const bool tw = lds_holds(sh + tables);
+#define IOBM_PL1(MM, TW)                                                                                             \
+  hipLaunchKernelGGL((k_plane_lds<T, MM, TW>), dim3(A.nplanes), dim3(256), sh + (TW ? tables : 0), c->stream, A, c->plan, \
+                     twx_of<T>(c), twy_of<T>(c))
+#define IOBM_PL(MM)              \
+  do {                           \
+    if (tw) IOBM_PL1(MM, true);  \
+    else IOBM_PL1(MM, false);    \
+  } while (0)
   switch (mode) {
     case PM_FULL: IOBM_PL(PM_FULL); break;
     case PM_INV: IOBM_PL(PM_INV); break;
@@ -1258,6 +1272,7 @@ hipError_t launch_plane(iobm_ctx c, int mode, const PlaneArgs<T>& A) {
     default: IOBM_PL(PM_ACC); break;
   }
 #undef IOBM_PL
+#undef IOBM_PL1
   return hipGetLastError();
 }
 

@@ -943,8 +943,10 @@ __global__ void __launch_bounds__(256) k_sigma_diag(const zd* __restrict__ sig, 
 //      [nz][MB] modes of one rhs,
 //   3. k_fft_planes: inverse 2D FFT in place, scaled by 1/Nxy.
 
-// Batched 2D FFT of the planes of the active rhs; block = (slot, plane).
-template <typename T>
+// Batched 2D FFT of the planes of the active rhs; block = (slot, plane).  TW:
+// the twiddle tables lie in LDS beside the two planes (lds_holds); otherwise
+// they are read from global memory.
+template <typename T, bool TW>
 __global__ void __launch_bounds__(256) k_fft_planes(FFTPlan2D plan, int nz, const cplx<T>* in,
                                                     cplx<T>* out, const cplx<T>* __restrict__ twx,
                                                     const cplx<T>* __restrict__ twy, int sign, T scale,
@@ -956,15 +958,17 @@ __global__ void __launch_bounds__(256) k_fft_planes(FFTPlan2D plan, int nz, cons
   const int nxy = plan.x.n * plan.y.n;
   cplx<T>* bufB = bufA + nxy;
   cplx<T>*tx = bufB + nxy, *ty = tx + plan.x.n;
-  for (int i = threadIdx.x; i < plan.x.n; i += blockDim.x) tx[i] = twx[i];
-  for (int i = threadIdx.x; i < plan.y.n; i += blockDim.x) ty[i] = twy[i];
+  if constexpr (TW) {
+    for (int i = threadIdx.x; i < plan.x.n; i += blockDim.x) tx[i] = twx[i];
+    for (int i = threadIdx.x; i < plan.y.n; i += blockDim.x) ty[i] = twy[i];
+  }
   const int slot = blockIdx.x / nz;
   const int z = blockIdx.x - slot * nz;
   const int rhs = rhs_of(active, slot);
   const long long off = (long long)rhs * nxy * nz + (long long)z * nxy;
   for (int p = threadIdx.x; p < nxy; p += blockDim.x) bufA[p] = in[off + p];
   __syncthreads();
-  cplx<T>* res = fft2d_lds(bufA, bufB, plan, tx, ty, sign);
+  cplx<T>* res = TW ? fft2d_lds(bufA, bufB, plan, tx, ty, sign) : fft2d_lds(bufA, bufB, plan, twx, twy, sign);
   double a = 0, b = 0, dummy = 0;
   for (int p = threadIdx.x; p < nxy; p += blockDim.x) {
     const cplx<T> v = scale * res[p];
@@ -1979,7 +1983,7 @@ static hipError_t launch_boundary(iobm_ctx c, const cplx<T>* x, cplx<T>* y, cplx
   }
   if (!reg) {
     const size_t twb = (size_t)(c->g.nx + c->g.ny) * sizeof(cplx<T>);
-    const int tw_lds = sh + twb + 1024 <= 160 * 1024;  // (1 KiB: the kernel's static arrays)
+    const int tw_lds = lds_holds(sh + twb);
 #define IOBM_BLDS(NF)                                                                                             \
   hipLaunchKernelGGL((k_boundary<T, TR, NF>), dim3(2 * nrhs), dim3(fft_threads(c->g.nxy)), sh + (tw_lds ? twb : 0), \
                      c->stream, c->plan, c->g.nz, x, y, rout, sigtab<T>(c), e_rhs, twx<T>(c), twy<T>(c), active,     \
@@ -2205,9 +2209,13 @@ hipError_t launch_fft_planes(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int si
   if (nrhs <= 0) return hipSuccess;
   const int rec = prof_start(c, dpart ? IOBM_K_FFT_PLANES_DOT : IOBM_K_FFT_PLANES);
   if (!fft_reg_dispatch<T>(c, in, out, sign, scale, nrhs, active, mvec, dpart)) {
-    size_t sh = (2 * (size_t)c->g.nxy + c->g.nx + c->g.ny) * sizeof(cplx<T>);
-    hipLaunchKernelGGL(k_fft_planes<T>, dim3(nrhs * c->g.nz), dim3(256), sh, c->stream, c->plan, c->g.nz, in, out,
-                       twx<T>(c), twy<T>(c), sign, (T)scale, active, dvec, dpart);
+    const size_t planes = 2 * (size_t)c->g.nxy * sizeof(cplx<T>), tables = (size_t)(c->g.nx + c->g.ny) * sizeof(cplx<T>);
+#define IOBM_FL(TW)                                                                                          \
+  hipLaunchKernelGGL((k_fft_planes<T, TW>), dim3(nrhs * c->g.nz), dim3(256), planes + (TW ? tables : 0), c->stream, \
+                     c->plan, c->g.nz, in, out, twx<T>(c), twy<T>(c), sign, (T)scale, active, dvec, dpart)
+    if (lds_holds(planes + tables)) IOBM_FL(true);
+    else IOBM_FL(false);
+#undef IOBM_FL
   }
   // streams: plain 2; with the dot 3 (read Z, R; write z)
   prof_stop(c, rec, (dpart ? 3.0 : 2.0) * nrhs * c->g.npts * sizeof(cplx<T>));

@@ -173,3 +173,39 @@ def test_size_limits(torch):
         ctx = C.c_void_p()
         assert lib.iobm_create(C.byref(g), None, C.byref(ctx)) == 0, (nx, ny, nz, nf)
         assert lib.iobm_destroy(ctx) == 0
+
+
+@pytest.mark.parametrize("nx,ny,centres", [(2, 2040, 0), (2, 2046, 0), (2048, 2, 0), (2016, 2, 32)])
+def test_long_thin_planes(torch, nx, ny, centres):
+    """Admitted planes of two lines whose twiddle tables do not fit the LDS beside two complex128 planes (with 128
+    projectors from 2 x 2016 on): the lateral-Fourier preconditioner is still the inverse of the flat-wire operator, and
+    the complex128 solve agrees with the complex64 one, whose tables fit.  Both stop at 1e-10 of the right-hand side:
+    psi to 1e-7 (1e-10 times the resolvent's norm, tens to hundreds away from thresholds).  The operator's and the
+    preconditioner's rounding is some 1e-16 times their norms (30 and a few hundred): 1e-11."""
+    from paper_1009_5300_amd import iobm
+    from workloads.synth import _kb_projectors
+    g = Grid(nx, ny, 6, 0.4, 1)
+    rng = np.random.default_rng(nx)
+    s = _solver(g, np.zeros(g.shape))
+    ids, _, _ = s.channels(0.1)
+    r = torch.as_tensor(rng.standard_normal((2,) + g.shape) + 1j * rng.standard_normal((2,) + g.shape), device="cuda")
+    z, rz = s.precondition(iobm.PC_LATERAL_FFT, r, E=0.1, want_rz=True)
+    assert float((s.apply(0.1, z) - r).abs().max()) <= 1e-11 * float(z.abs().max())
+    ref = (r * z).flatten(1).sum(1).cpu().numpy()
+    assert np.abs(rz - ref).max() <= 1e-11 * float((r * z).abs().sum())
+    s.set_potential(0.05 * rng.random(g.shape))
+    if centres:
+        L = max(nx, ny) * 0.4
+        at = [np.array([(a + 0.5) * L / centres, 0.3, 1.0]) for a in range(centres)]
+        s.set_nonlocal(_kb_projectors(g, at, 0.5, 4, rng))
+    pick = [[int(m) for m in ids[:3]]]
+    out = [s.solve([0.1], channels=pick, opts=iobm.default_opts(precision=p), want_psi=True)
+           for p in (iobm.C128, iobm.C64_REFINED)]
+    assert [o["status"] for o in out] == [0, 0]
+    a, b = (o["psi"] for o in out)
+    assert float((a - b).abs().max()) <= 1e-7 * float(b.abs().max())
+    if not centres:
+        kap = (0.0, 0.3 * np.pi / (ny * 0.4)) if ny > nx else (0.3 * np.pi / (nx * 0.4), 0.0)
+        S = [s.smatrix_bloch([0.01], kap, opts=iobm.default_opts(precision=p)) for p in (iobm.C128, iobm.C64_REFINED)]
+        assert S[0][3] == 0 and S[1][3] == 0 and S[0][0][0].size > 0
+        assert np.abs(S[0][0][0] - S[1][0][0]).max() <= 1e-7
