@@ -386,8 +386,9 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   // (r is its slot 0), Z / W and, in complex128, the folded correction; the
   // folded direction (and correction, in complex64) share r_hi, which is
   // written only when a replacement has consumed them
-  const bool modal = o.precond == IOBM_PC_LATERAL_FFT;
+  bool modal = o.precond == IOBM_PC_LATERAL_FFT;
   cplx<T>* d = (cplx<T>*)workspace(ctx, S_D, vb);
+  cplx<T>* pf = modal ? (cplx<T>*)workspace(ctx, S_PF, vb) : nullptr;
   cplx<T>* r = (cplx<T>*)workspace(ctx, S_R, vb);
   cplx<T>* pa = (cplx<T>*)workspace(ctx, S_P, vb);   // direction, two buffers used in turn
   cplx<T>* pb = (cplx<T>*)workspace(ctx, S_P2, vb);
@@ -404,9 +405,9 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   Modal<T> MD;
   constexpr int kRing = ModalRing<T>::n;
   if (modal) {
-    cplx<T>* vecs[7] = {r, z, pa, pb, q, d, (cplx<T>*)workspace(ctx, S_PF, vb)};
+    cplx<T>* vecs[6] = {r, z, pa, pb, q, d};
     for (int i = 0; i < kRing; ++i) MD.ring[i] = vecs[i];
-    MD.w = vecs[6];
+    MD.w = pf;
     MD.fold_s = (cplx<T>*)rhi;
     if (kRing == 6) {
       MD.fold_t = MD.fold_s + vol;
@@ -470,6 +471,8 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   auto precond = [&](int nact, const int* ad) {
     if (o.precond == IOBM_PC_TRUNCATED_LAPLACIAN)
       HIPCHK(launch_precond_laplacian<T>(ctx, o.alpha, r, z, nact, ad, part_rz));
+    else if (o.precond == IOBM_PC_LATERAL_FFT)
+      HIPCHK(launch_precond_fft<T>(ctx, r, z, pf, nact, e_d, modes, ad, part_rz));
     else if (o.precond == IOBM_PC_JACOBI)
       HIPCHK(launch_precond_jacobi<T>(ctx, r, z, nact, e_d, E_d, ad, part_rz));
     else
@@ -487,6 +490,7 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
   std::vector<int> since(nb, 0);  // steps since the last replacement, per rhs (d holds data from 2 on)
   std::vector<char> kept(nb, 0);  // the last replacement kept the direction (p_old is read at its first step)
   std::vector<char> badv(nb, 0);  // breakdown or divergence seen at the last check
+  std::vector<char> goes(nb, 0);  // leaves the mode-space iteration at its refinement
   cplx<T>* pold = pa;  // the direction of the last step (its update pending)
   cplx<T>* pnew = pb;
   // Refinement of the listed rhs: x += d + alpha p, d = 0, r = b - A x in FP64 (stored
@@ -645,13 +649,39 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
     HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->cap_ev[1], 0));
     if (!modal && check % 2) std::swap(pold, pnew);
   };
-  while (nact > 0) {
+  // A state that breaks down or diverges in mode space, or takes this many
+  // steps without a replacement, goes on with the recurrence that applies the
+  // operator once the others are done.  In complex64 the rounding of q_old
+  // (modal.hip) can stop a hard state: of 2,868 states of eight grids with
+  // wells of 0.8 to 5, 11 were not at 1e-10 after 6,000 steps, where the
+  // operator's recurrence takes at most 5,750.  With the hand-over all of 7,556
+  // states of the hardest four converge (the operator's recurrence alone leaves
+  // 4 of them), in 32 s where that takes 52.  (Chains, wires and weaker wells
+  // need 10 to 100 steps a replacement.)  Complex128 replaces at the end only;
+  // its longest solve took 4,018 steps in mode space and 3,920 with the operator.
+  constexpr int kHandOver = sizeof(T) == sizeof(float) ? 512 : 16384;
+  std::vector<int> hand;
+  while (nact > 0 || !hand.empty()) {
+    if (nact == 0) {  // r holds the true residuals of their last refinement
+      modal = false;
+      cg.reset();
+      act.swap(hand);
+      std::sort(act.begin(), act.end());
+      nact = (int)act.size();
+      act_d = upload(ctx, S_IDX, act, 64 * 1024);
+      restart(nact, act_d);
+      for (int i : act) {
+        since[i] = 0;
+        decay[i] = 0.0;
+      }
+      if (adapt) check = 1;
+    }
     run_check();
     for (int i : act) since[i] += check;
     HIPCHK(hipMemcpyAsync(rbh, rn2, check_bytes, hipMemcpyDeviceToHost, ctx->stream));
     stream_sync(ctx);
     // which rhs fold their correction into x and refresh the residual
-    std::vector<int> upd;
+    std::vector<int> upd, drop;
     for (int i : act) {
       out.iters[i] += check;
       const double r2 = rn2_h[i];
@@ -661,9 +691,17 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
       obs_it[i] = 0;
       const bool bad = flag_h[i] || !(r2 == r2) || r2 > 1e4 * maxr2[i];  // breakdown or divergence
       badv[i] = bad;
-      if (bad || r2 <= 0.25 * tol2 * bn2[i] || r2 <= delta2 * maxr2[i] || out.iters[i] >= o.max_iter)
-        upd.push_back(i);
+      const bool reached = r2 <= 0.25 * tol2 * bn2[i] || r2 <= delta2 * maxr2[i];
+      const bool slow = modal && !reached && since[i] >= kHandOver;
+      if (bad || reached || slow || out.iters[i] >= o.max_iter) upd.push_back(i);
       else maxr2[i] = std::max(maxr2[i], r2);
+      // a correction that raised the residual is not taken along
+      goes[i] = modal && (bad || slow);
+      if (goes[i] && !(r2 < tn2_h[i])) drop.push_back(i);
+    }
+    if (!drop.empty()) {
+      HIPCHK(modal_drop<T>(ctx, MD, (int)drop.size(), upload(ctx, S_IDX, drop, 72 * 1024)));
+      for (int i : drop) since[i] = 0;
     }
     if (!upd.empty()) {
       refresh(upd, 7);
@@ -679,8 +717,12 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
           out.status[i] = flag_h[i] ? IOBM_E_BREAKDOWN : IOBM_E_NOT_CONVERGED;
           continue;
         }
-        (keep_dir && !badv[i] && improved && since[i] > 0 ? keep : rst).push_back(i);
         maxr2[i] = t2;
+        if (goes[i]) {
+          hand.push_back(i);
+          continue;
+        }
+        (keep_dir && !badv[i] && improved && since[i] > 0 ? keep : rst).push_back(i);
       }
       std::vector<char> gone(nb, 0);
       for (int i : upd) gone[i] = 1;

@@ -108,6 +108,10 @@ hipError_t modal_step(iobm_ctx c, const Modal<T>& M, int nact, const int* active
 template <typename T>
 hipError_t modal_correct(iobm_ctx c, const Modal<T>& M, zd* x, const int* xset, int nact, const int* active,
                          double ring_reads, int nfirst);
+// forget the steps of the listed rhs since the last replacement (their
+// correction is then zero)
+template <typename T>
+hipError_t modal_drop(iobm_ctx c, const Modal<T>& M, int nact, const int* active);
 // |r|^2 and breakdown flags of the listed rhs
 template <typename T>
 hipError_t modal_check(iobm_ctx c, const Modal<T>& M, int nact, const int* active, double* rn2, int* flag);

@@ -1131,6 +1131,15 @@ __global__ void k_ring_rebase(ModalScal* sc, const int* active, int nact, int nr
   if (s.step + 1 - s.base == nr - 1) s.base = s.step + 1;
 }
 
+// No steps since the last replacement.
+__global__ void k_modal_drop(ModalScal* sc, const int* active, int nact) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nact) return;
+  ModalScal& s = sc[rhs_of(active, i)];
+  s.step = -1;
+  s.base = 0;
+}
+
 // |r|^2 and the breakdown flag of the last mode pass per right-hand side,
 // for the host's convergence check.
 __global__ void __launch_bounds__(256) k_modal_check(const ModalScal* __restrict__ sc, const double* __restrict__ part,
@@ -1458,6 +1467,13 @@ hipError_t modal_correct(iobm_ctx c, const Modal<T>& M, zd* x, const int* xset, 
 }
 
 template <typename T>
+hipError_t modal_drop(iobm_ctx c, const Modal<T>& M, int nact, const int* active) {
+  if (nact <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_modal_drop, dim3((nact + 255) / 256), dim3(256), 0, c->stream, M.sc, active, nact);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t modal_check(iobm_ctx c, const Modal<T>& M, int nact, const int* active, double* rn2, int* flag) {
   if (nact <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_modal_check, dim3((nact + 3) / 4), dim3(256), 0, c->stream, M.sc, M.part, M.nmb, active, nact,
@@ -1470,6 +1486,7 @@ hipError_t modal_check(iobm_ctx c, const Modal<T>& M, int nact, const int* activ
   template hipError_t modal_start<T>(iobm_ctx, const Modal<T>&, int, const int*);                                \
   template hipError_t modal_step<T>(iobm_ctx, const Modal<T>&, int, const int*, bool);                           \
   template hipError_t modal_correct<T>(iobm_ctx, const Modal<T>&, zd*, const int*, int, const int*, double, int); \
+  template hipError_t modal_drop<T>(iobm_ctx, const Modal<T>&, int, const int*);                                  \
   template hipError_t modal_check<T>(iobm_ctx, const Modal<T>&, int, const int*, double*, int*);
 IOBM_MODAL_INST(float)
 IOBM_MODAL_INST(double)

@@ -82,3 +82,28 @@ def test_iterations_of_a_chain_stay_bounded(torch, seed):
     out = state["solver"].solve(state["E"], opts=state["opts"])
     assert out["status"] == 0
     assert max(st[0] for st in np.array(out["stats"])) <= 510
+
+
+@pytest.mark.parametrize("n,m,nz,nf,h,depth,seeds", [(12, 12, 64, 1, 0.5, 3.0, (4, 11)), (10, 9, 48, 2, 0.5, 2.0, (5, 22)),
+                                                     (12, 12, 48, 3, 0.35, 5.0, (3, 6, 7, 13))])
+def test_states_that_stagnate_in_mode_space(torch, n, m, nz, nf, h, depth, seeds):
+    """Deep wells whose complex64 states need up to a thousand steps a replacement: the mode-space recurrence alone
+    leaves states of each grid above 1e-10 at 6,000 steps, where the one that applies the operator takes at most 5,750
+    on such potentials.  Each converges within 8,000, and psi to the complex128 solve's: both stop at 1e-10 of the
+    right-hand side, and these wells' resolvents are some 1e3 in these units: 1e-6 of the largest |psi|."""
+    from paper_1009_5300_amd import iobm
+    s = iobm.Solver(n, m, nz, (h, h, h), nf)
+    for seed in seeds:
+        rng = np.random.default_rng(seed)
+        k, j, i = np.meshgrid(np.arange(nz), np.arange(m), np.arange(n), indexing="ij")
+        V = 0.02 * rng.uniform(-1, 1, (nz, m, n))
+        for f in (0.3, 0.7):
+            V -= depth * np.exp(-(((i - n / 2) * h) ** 2 + ((j - m / 2) * h) ** 2 + ((k - f * nz) * h) ** 2) / 4.5)
+        s.set_potential(V)
+        E = list(rng.uniform(0.1, 1.0, 6))
+        for graph in (0, 1):
+            out = s.solve(E, opts=iobm.default_opts(precision=iobm.C64_REFINED, max_iter=8000, graph=graph), want_psi=True)
+            assert out["status"] == 0, (seed, graph, max(st[0] for st in out["stats"]))
+        ref = s.solve(E, opts=iobm.default_opts(precision=iobm.C128), want_psi=True)
+        assert ref["status"] == 0
+        assert float((out["psi"] - ref["psi"]).abs().max()) <= 1e-6 * float(ref["psi"].abs().max())
