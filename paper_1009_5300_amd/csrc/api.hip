@@ -1433,9 +1433,8 @@ void solve_pair_batch(iobm_ctx ctx, const iobm_solve_opts& o, const BlochPhase& 
   auto read_back = [&]() {
     HIPCHK(hipMemcpyAsync(rbh, rn2, (size_t)ns * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipMemcpyAsync(rbh + (size_t)ns * sizeof(double), flag,
-                          (size_t)(modal ? ns : np) * sizeof(int), hipMemcpyDeviceToHost,  // per slot in mode space
-                         
-                          ctx->stream));
+                          (size_t)(modal ? ns : np) * sizeof(int),  // per slot in mode space
+                          hipMemcpyDeviceToHost, ctx->stream));
     stream_sync(ctx);
   };
 
@@ -1447,13 +1446,13 @@ void solve_pair_batch(iobm_ctx ctx, const iobm_solve_opts& o, const BlochPhase& 
   read_back();
   std::vector<double> bn2(rn2_h, rn2_h + ns), last(bn2);
   std::vector<int> it(np, 0), rs(np, 0);
-  auto finish = [&](int k, int status) {
+  auto finish = [&](int k, int status, const double* r2) {  // r2: |r|^2 of the x that stays
     for (int s2 = 0; s2 < 2; ++s2) {
       const int sl = 2 * k + s2;
       out.iters[sl] = it[k];
       out.refin[sl] = rs[k];
       out.status[sl] = status;
-      out.rel[sl] = bn2[sl] > 0 ? sqrt(rn2_h[sl] / bn2[sl]) : 0.0;
+      out.rel[sl] = bn2[sl] > 0 ? sqrt(r2[sl] / bn2[sl]) : 0.0;
     }
   };
   auto pair_conv = [&](int k) {
@@ -1471,8 +1470,8 @@ void solve_pair_batch(iobm_ctx ctx, const iobm_solve_opts& o, const BlochPhase& 
   {  // right-hand sides that vanish, or a first rho that vanishes
     std::vector<int> keep;
     for (int k : act) {
-      if (pair_conv(k)) finish(k, IOBM_OK);
-      else if (!modal && flag_h[k]) finish(k, IOBM_E_BREAKDOWN);
+      if (pair_conv(k)) finish(k, IOBM_OK, rn2_h);
+      else if (!modal && flag_h[k]) finish(k, IOBM_E_BREAKDOWN, rn2_h);
       else keep.push_back(k);
     }
     if (keep.size() != act.size()) {
@@ -1481,46 +1480,44 @@ void solve_pair_batch(iobm_ctx ctx, const iobm_solve_opts& o, const BlochPhase& 
     }
   }
   const int max_restarts = 1000;
-  // A pair that breaks down or diverges in mode space, or takes this many
-  // steps without a replacement, goes on with the recurrence that applies the
-  // operator, from the x of its last replacement, once the others are done.
-  // (Of 1,260 states of a 12 x 12 x 64 grid with wells of 1.5, where that
-  // recurrence takes 210 steps in all on average, 5 stagnated in mode space and
-  // 1 of them there as well.)
+  // A pair that has taken this many steps in mode space since its last
+  // replacement takes one where both residuals have fallen tenfold.  Otherwise,
+  // and after a breakdown or divergence, it goes on with the recurrence that
+  // applies the operator, from the x of its last replacement, once the others
+  // are done.  (Of 1,100 pairs of a 12 x 12 x 64 grid with wells of 1.5 that
+  // recurrence alone leaves 1, this none.  Of 4,790 pairs of three grids with
+  // wells of 2 and 3, limited to 5,000 steps, it leaves 480, this 367; 472 where
+  // every correction is folded in before the change, 380 where none is.)
   constexpr int kHandOver = 512;
   std::vector<int> hand;
   while (!act.empty() || !hand.empty()) {
-    if (act.empty()) {
+    std::vector<int> keep, redo, stop;
+    if (act.empty()) {  // the handed-over pairs, with nothing pending
       modal = false;
-      act.swap(hand);
-      set_lists(act);
+      redo.swap(hand);
       HIPCHK(hipMemsetAsync(d, 0, vb, ctx->stream));
       HIPCHK(hipMemsetAsync(rho, 0, (size_t)np * 3 * sizeof(zd), ctx->stream));
-      restart(act);
-      nfresh = 2 * (int)act.size();
+    } else {
+      const int npr = (int)act.size();
+      for (int c2 = 0; c2 < check; ++c2) iterate(act);
+      if (modal) HIPCHK(modal_check<T>(ctx, MD, 2 * npr, sl_d, rn2, flag));
+      for (int k : act) it[k] += check;
       read_back();
-      for (int k : act) {
-        last[2 * k] = rn2_h[2 * k];
-        last[2 * k + 1] = rn2_h[2 * k + 1];
-      }
     }
-    const int npr = (int)act.size();
-    for (int c2 = 0; c2 < check; ++c2) iterate(act);
-    if (modal) HIPCHK(modal_check<T>(ctx, MD, 2 * npr, sl_d, rn2, flag));
-    for (int k : act) it[k] += check;
-    read_back();
-    std::vector<int> keep, redo, stop;
     for (int k : act) {
       const double a = rn2_h[2 * k], c3 = rn2_h[2 * k + 1];
       const bool bad = flag_h[modal ? 2 * k : k] || !std::isfinite(a) || !std::isfinite(c3) || a > 1e20 * bn2[2 * k] ||
                        c3 > 1e20 * bn2[2 * k + 1];
-      const bool done = !bad && (pair_conv(k) || pair_replace(k));
-      if (modal && !done && (bad || since[k] >= kHandOver)) hand.push_back(k);
-      else if (bad || done) redo.push_back(k);
-      else if (it[k] >= o.max_iter) {
-        finish(k, IOBM_E_NOT_CONVERGED);
+      const bool over = it[k] >= o.max_iter, late = modal && since[k] >= kHandOver;
+      const bool fell = a < 1e-2 * last[2 * k] && c3 < 1e-2 * last[2 * k + 1];  // |r|^2
+      if (!bad && (pair_conv(k) || pair_replace(k) || (late && fell))) redo.push_back(k);
+      else if (bad && !modal) redo.push_back(k);
+      else if (bad && over) finish(k, IOBM_E_NOT_CONVERGED, last.data());  // x of the last replacement
+      else if (over) {
+        finish(k, IOBM_E_NOT_CONVERGED, rn2_h);
         stop.push_back(k);
-      } else keep.push_back(k);
+      } else if (bad || late) hand.push_back(k);
+      else keep.push_back(k);
     }
     if (!stop.empty()) {  // fold in the pending correction of the pairs that stop here
       set_lists(stop);
@@ -1535,9 +1532,9 @@ void solve_pair_batch(iobm_ctx ctx, const iobm_solve_opts& o, const BlochPhase& 
         ++rs[k];
         last[2 * k] = rn2_h[2 * k];
         last[2 * k + 1] = rn2_h[2 * k + 1];
-        if (pair_conv(k)) finish(k, IOBM_OK);
-        else if ((!modal && flag_h[k]) || rs[k] >= max_restarts) finish(k, IOBM_E_BREAKDOWN);
-        else if (it[k] >= o.max_iter) finish(k, IOBM_E_NOT_CONVERGED);
+        if (pair_conv(k)) finish(k, IOBM_OK, rn2_h);
+        else if ((!modal && flag_h[k]) || rs[k] >= max_restarts) finish(k, IOBM_E_BREAKDOWN, rn2_h);
+        else if (it[k] >= o.max_iter) finish(k, IOBM_E_NOT_CONVERGED, rn2_h);
         else {
           keep.push_back(k);
           nfresh += 2;
@@ -1551,7 +1548,8 @@ void solve_pair_batch(iobm_ctx ctx, const iobm_solve_opts& o, const BlochPhase& 
     }
   }
   // every pair ended right after a restart or a stop, each of which folded
-  // in its pending correction: x holds the solution
+  // in its pending correction, or at the iteration limit with a breakdown in
+  // mode space, whose correction is dropped: x holds the solution
 }
 
 }  // namespace
