@@ -649,14 +649,16 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
     HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->cap_ev[1], 0));
     if (!modal && check % 2) std::swap(pold, pnew);
   };
-  // A state that breaks down or diverges in mode space, or takes this many
-  // steps without a replacement, goes on with the recurrence that applies the
-  // operator once the others are done.  In complex64 the rounding of q_old
+  // A state that has taken this many steps in mode space since its last
+  // replacement takes one where its residual has fallen tenfold.  Otherwise, and
+  // after a breakdown or divergence, it goes on with the recurrence that applies
+  // the operator once the others are done.  In complex64 the rounding of q_old
   // (modal.hip) can stop a hard state: of 2,868 states of eight grids with
   // wells of 0.8 to 5, 11 were not at 1e-10 after 6,000 steps, where the
-  // operator's recurrence takes at most 5,750.  With the hand-over all of 7,556
-  // states of the hardest four converge (the operator's recurrence alone leaves
-  // 4 of them), in 32 s where that takes 52.  (Chains, wires and weaker wells
+  // operator's recurrence takes at most 5,750.  With this rule all of 7,556
+  // states of the hardest four converge, in at most 8,018 steps and 28 s (the
+  // operator's recurrence alone leaves 4 of them at 50,000 and takes 52 s; without
+  // the replacement at a tenth 20,671 steps).  (Chains, wires and weaker wells
   // need 10 to 100 steps a replacement.)  Complex128 replaces at the end only;
   // its longest solve took 4,018 steps in mode space and 3,920 with the operator.
   constexpr int kHandOver = sizeof(T) == sizeof(float) ? 512 : 16384;
@@ -692,11 +694,11 @@ void solve_rhs_batch(iobm_ctx ctx, const iobm_solve_opts& o, const Batch& B, con
       const bool bad = flag_h[i] || !(r2 == r2) || r2 > 1e4 * maxr2[i];  // breakdown or divergence
       badv[i] = bad;
       const bool reached = r2 <= 0.25 * tol2 * bn2[i] || r2 <= delta2 * maxr2[i];
-      const bool slow = modal && !reached && since[i] >= kHandOver;
-      if (bad || reached || slow || out.iters[i] >= o.max_iter) upd.push_back(i);
+      const bool late = modal && since[i] >= kHandOver;
+      if (bad || reached || late || out.iters[i] >= o.max_iter) upd.push_back(i);
       else maxr2[i] = std::max(maxr2[i], r2);
       // a correction that raised the residual is not taken along
-      goes[i] = modal && (bad || slow);
+      goes[i] = modal && (bad || (late && !reached && !(r2 < 1e-2 * tn2_h[i])));
       if (goes[i] && !(r2 < tn2_h[i])) drop.push_back(i);
     }
     if (!drop.empty()) {
