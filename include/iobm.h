@@ -362,7 +362,10 @@ iobm_status iobm_grad_transmission(iobm_ctx ctx, const iobm_solve_opts* opts, in
  *                      1 = the z filter (each mode beside its negative in one
  *                      wavefront; used where its pair blocks fit the nz
  *                      partial slots of a state), 2 = the inverse plane FFT
- *                      (iobm_precondition with r^T z; default 1 where it fits)
+ *                      (iobm_precondition with r^T z; default 1 where it fits,
+ *                      but 2 in complex128 with chunks of 32 planes, and in
+ *                      complex64 for nf = 2 on 48 x 48 points with more than
+ *                      80 planes: the faster pass there)
  * Shapes are kept per kernel arithmetic: IOBM_C64_REFINED selects the
  * complex64 kernels of the inner iteration, IOBM_C128 the complex128 ones
  * (including the FP64 residual refresh of a IOBM_C64_REFINED solve).

@@ -2259,21 +2259,36 @@ static hipError_t launch_zfilter(iobm_ctx c, int L, const cplx<T>* in, cplx<T>* 
   return hipGetLastError();
 }
 
-// The z filter takes the r^T z partials when the plane transforms are the
-// register ones (natural mode order, R in the scratch that feeds the filter),
-// its pair blocks fit the nz partial slots of a rhs, and the launch shape
-// does not name the inverse transform (rz_pass 2).
-static bool zfilter_dot_fits(iobm_ctx c) { return c->zpair_nmb > 0 && c->zpair_nmb <= c->g.nz; }
-template <typename T>
-static bool zfilter_dot_ok(iobm_ctx c) {
-  return zfilter_dot_fits(c) && fft_reg_available<T>(c) && c->shape[prec_index<T>()].rz_pass != 2;
-}
-
 static int default_zfilter_chunk(iobm_ctx c) {
   // at most 8 chunks (512 threads per block)
   int L = 16;
   if ((c->g.nz + L - 1) / L > 8) L = 32;
   return L;
+}
+
+// The z filter can take the r^T z partials when the plane transforms are the
+// register ones (natural mode order, R in the scratch that feeds the filter)
+// and its pair blocks fit the nz partial slots of a rhs.  It does where the
+// launch shape does not name a pass, except where its paired variant is the
+// slower one: complex128 with chunks of 32 planes, where its registers spill
+// (the call: 48 vectors of 48 x 48 x 200 769 us, 653 with the inverse
+// transform's partials; 16 of 24 x 24 x 160 100 and 89; with chunks of 16
+// 356 and 388 us for 100 of 32 x 32 x 128), and in complex64 the 4th-order
+// filter with six and more chunks of 16 planes on 48 x 48 points (96 vectors,
+// 128 planes 406 and 369 us, 96 planes 335 and 307; 64 planes 182 and 190; on 32 x 32 x
+// 128 191 and 186 with 100 vectors, 56 and 60 with 8).
+static bool zfilter_dot_fits(iobm_ctx c) { return c->zpair_nmb > 0 && c->zpair_nmb <= c->g.nz; }
+static bool zfilter_dot_chosen(iobm_ctx c, int prec) {
+  const iobm_launch_shape& s = c->shape[prec];
+  if (!zfilter_dot_fits(c)) return false;
+  if (s.rz_pass) return s.rz_pass == 1;
+  const int L = s.zfilter_chunk > 0 ? s.zfilter_chunk : default_zfilter_chunk(c);
+  if (prec == prec_index<double>()) return L != 32;
+  return !(c->g.nf == 2 && c->g.nx >= 48 && L == 16 && c->g.nz > 5 * L);
+}
+template <typename T>
+static bool zfilter_dot_ok(iobm_ctx c) {
+  return fft_reg_available<T>(c) && zfilter_dot_chosen(c, prec_index<T>());
 }
 
 template <typename T>
@@ -2397,7 +2412,7 @@ iobm_launch_shape launch_shape_in_effect(iobm_ctx c, int prec) {
   r.planes_per_block = r.stencil == 1 ? (s.planes_per_block > 0 ? s.planes_per_block : 32) : 16;
   r.zfilter_chunk = s.zfilter_chunk > 0 ? s.zfilter_chunk : default_zfilter_chunk(c);
   r.plane_fft = (square_reg_size(c) && s.plane_fft != 2) ? 1 : 2;
-  r.rz_pass = (r.plane_fft == 1 && zfilter_dot_fits(c) && s.rz_pass != 2) ? 1 : 2;
+  r.rz_pass = (r.plane_fft == 1 && zfilter_dot_chosen(c, prec)) ? 1 : 2;
   return r;
 }
 

@@ -402,3 +402,20 @@ def test_jacobi_preconditioner(torch, g, kb):
         assert np.abs(z - ref).max() <= tol * np.abs(ref).max()
         a, b = r.reshape(3, -1), ref.reshape(3, -1)
         assert np.all(np.abs(rz - (a * b).sum(axis=1)) <= 10 * tol * (np.abs(a) * np.abs(b)).sum(axis=1))
+
+
+@pytest.mark.parametrize("n,nz,nf,c128,c64", [(48, 80, 2, 1, 1), (48, 81, 2, 1, 2), (48, 81, 1, 1, 1), (32, 96, 2, 1, 1),
+                                              (8, 128, 2, 1, 1), (8, 129, 2, 2, 1), (48, 129, 2, 2, 1), (48, 24, 2, 2, 2)])
+def test_default_rz_pass(torch, n, nz, nf, c128, c64):
+    """The pass that forms the r^T z partials when none is pinned, on both sides of its rule's lines, and its sum against
+    torch's.  Two transforms' rounding lies between them (some 4e-7 of the sum of moduli in complex64): 2e-6 and
+    1e-13 of it."""
+    from paper_1009_5300_amd import iobm
+    g = Grid(n, n, nz, 0.4, nf)
+    s = _solver(g, np.zeros(g.shape))
+    r = torch.as_tensor(random_field((2,) + g.shape, 7), device="cuda")
+    for prec, rr, want, tol in ((iobm.C128, r, c128, 1e-13), (iobm.C64_REFINED, r.to(torch.complex64), c64, 2e-6)):
+        assert s.get_launch_shape(prec)["rz_pass"] == want
+        z, rz = s.precondition(iobm.PC_LATERAL_FFT, rr, E=1.3, precision=prec, want_rz=True)
+        p = rr.to(torch.complex128) * z.to(torch.complex128)
+        assert np.abs(rz - p.flatten(1).sum(1).cpu().numpy()).max() <= tol * float(p.abs().flatten(1).sum(1).max())
