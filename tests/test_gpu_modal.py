@@ -107,3 +107,33 @@ def test_states_that_stagnate_in_mode_space(torch, n, m, nz, nf, h, depth, seeds
         ref = s.solve(E, opts=iobm.default_opts(precision=iobm.C128), want_psi=True)
         assert ref["status"] == 0
         assert float((out["psi"] - ref["psi"]).abs().max()) <= 1e-6 * float(ref["psi"].abs().max())
+
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["c128", "c64"])
+@pytest.mark.parametrize("n,nz,nf,depth,rank", [(48, 9, 2, 0.2, 0), (48, 9, 1, 0.6, 2), (24, 15, 2, 0.6, 4), (32, 7, 3, 0.2, 2)])
+def test_wide_planes(torch, n, nz, nf, depth, rank, precision):
+    """The largest register planes, with and without the nonlocal term (in complex128 two lanes share a line from 24
+    points on, and the mirror lines of the transform are exchanged between them).  An odd number of states and of
+    planes: the last block of 48 x 48 planes in complex128 and of 24 x 24 ones holds a plane past the last.  psi in
+    the oracle's own system, as above."""
+    from paper_1009_5300_amd import iobm
+    g = Grid(n, n, nz, 0.45, nf, hz_=0.5)
+    rng = np.random.default_rng(n + nz + nf)
+    V = _potential(g, depth, rng)
+    nl = None
+    if rank:
+        centres = [np.array([g.nx * g.hx / 2, g.ny * g.hy / 2, f * g.nz * g.hz]) for f in (0.3, 0.7)]
+        nl = _kb_projectors(g, centres, 0.6, rank, rng)
+    P = O.Problem(g, V, nl)
+    s = iobm.Solver(g.nx, g.ny, g.nz, g.spacings, g.nf)
+    s.set_potential(V)
+    if nl is not None:
+        s.set_nonlocal(nl)
+    out = s.solve([0.35], opts=iobm.default_opts(precision=precision), want_psi=True)
+    assert out["status"] == 0, out.get("error")
+    assert len(out["T"]) % 2 == 1
+    psi = out["psi"].cpu().numpy().reshape(len(out["T"]), -1)
+    for k, m in enumerate(out["modes"][0]):
+        b = P.rhs(0.35, int(m), "L").ravel()
+        assert np.linalg.norm(P.apply(0.35, psi[k]).ravel() - b) <= 1e-9 * np.linalg.norm(b), int(m)
+    assert np.abs(out["T"] + out["R"] - 1).max() <= 1e-7

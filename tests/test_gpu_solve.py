@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from workloads import Grid, make
+from workloads import Grid, make, random_field
 
 pytestmark = pytest.mark.gpu
 
@@ -482,3 +482,53 @@ def test_block_cocg_needs_complex128(torch):
     with pytest.raises(iobm.IobmError) as e:
         s.solve(list(w.energies[:2]), opts=iobm.default_opts(precision=iobm.C64_REFINED, block=1))
     assert e.value.status == 8 and "complex128" in str(e.value)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_pinned_tuned_stencil_is_bit_identical_across_contexts(torch, precision):
+    """A solve with Eq. (17), whose stencil shape the autotuner chooses: a second context with that shape pinned keeps it
+    through its own solve, and gives the first one's T, R, psi and iteration counts bit for bit."""
+    from paper_1009_5300_amd import iobm
+    w = make(4, Grid(24, 24, 24, 0.4, 2))
+    prec = (iobm.C128, iobm.C64_REFINED)[precision]
+    o = iobm.default_opts(precision=prec, precond=iobm.PC_TRUNCATED_LAPLACIAN)
+    s1, s2 = _solver(w), _solver(w)
+    a = s1.solve([0.3], opts=o, want_psi=True)
+    tuned = s1.get_launch_shape(prec)
+    assert tuned["stencil"] == 1 and tuned["points_per_thread"] in (1, 2, 3) and tuned["planes_per_block"] in (16, 32, 64)
+    for p in (iobm.C128, iobm.C64_REFINED):
+        s2.set_launch_shape(p, s1.get_launch_shape(p))
+    b, c = (s.solve([0.3], opts=o, want_psi=True) for s in (s1, s2))
+    assert s2.get_launch_shape(prec) == tuned
+    for out in (b, c):
+        assert out["status"] == 0 and a["status"] == 0
+        assert np.array_equal(out["T"], a["T"]) and np.array_equal(out["R"], a["R"])
+        assert torch.equal(out["psi"], a["psi"])
+        assert [st[0] for st in out["stats"]] == [st[0] for st in a["stats"]]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_pinned_zfilter_shapes_are_bit_identical_across_contexts(torch, precision):
+    """zfilter_chunk and rz_pass act in iobm_precondition: z and r^T z of two contexts with the same pin agree bit for
+    bit, and those of different pins to the rounding of a recursion over 40 planes and of two plane transforms (some 60
+    roundings, 7e-15 and 4e-6: 1e-13 and 1e-5 of the largest value, of the sum of moduli for r^T z)."""
+    from paper_1009_5300_amd import iobm
+    g = Grid(48, 48, 40, 0.4, 2)
+    prec, dt, tol = ((iobm.C128, torch.complex128, 1e-13), (iobm.C64_REFINED, torch.complex64, 1e-5))[precision]
+    r = torch.as_tensor(random_field((3,) + g.shape, 5), device="cuda").to(dt)
+    ref = None
+    for chunk in (8, 16, 32):
+        for rz_pass in (1, 2):
+            got = []
+            for _ in range(2):
+                s = iobm.Solver(g.nx, g.ny, g.nz, g.spacings, g.nf)
+                s.set_potential(np.zeros(g.shape))
+                s.set_launch_shape(prec, {"zfilter_chunk": chunk, "rz_pass": rz_pass})
+                assert s.get_launch_shape(prec)["zfilter_chunk"] == chunk and s.get_launch_shape(prec)["rz_pass"] == rz_pass
+                got.append(s.precondition(iobm.PC_LATERAL_FFT, r, E=0.8, precision=prec, want_rz=True))
+            (z1, p1), (z2, p2) = got
+            assert torch.equal(z1, z2) and np.array_equal(p1, p2)
+            if ref is None:
+                ref = (z1, p1)
+            assert float((z1 - ref[0]).abs().max()) <= tol * float(ref[0].abs().max())
+            assert np.abs(p1 - ref[1]).max() <= tol * float((r * ref[0]).abs().flatten(1).sum(1).max())
