@@ -348,8 +348,10 @@ iobm_status iobm_grad_transmission(iobm_ctx ctx, const iobm_solve_opts* opts, in
  *                      ceil(nx*ny / ppt) threads, which must fit the variant's
  *                      bound (1024, 1024, 768 and 640 threads)
  *   planes_per_block:  2.5D stencil, 8, 16, 32 or 64: the longest z chunk of a
- *                      block (small batches get shorter chunks, so that every
- *                      compute unit has blocks)
+ *                      block (default 32; small batches get shorter chunks, so
+ *                      that every compute unit has blocks, and iobm_apply and
+ *                      the residuals chunks of 16 where a launch's last round
+ *                      of blocks would leave much of the chip idle)
  *   zfilter_chunk:     lateral-Fourier preconditioner, 8, 16 or 32 planes per
  *                      chunk of the z recursion (at most 8 chunks) in
  *                      iobm_precondition, block COCG and the complex128

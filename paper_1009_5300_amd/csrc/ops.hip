@@ -1906,11 +1906,42 @@ static bool launch_apply25_shape(iobm_ctx c, int ppt, int zc, const Op& op, int 
   return true;
 }
 
-static int default_ppt(iobm_ctx c) {
-  // the fewest points per thread that fit: the smallest register window
+// Points per thread when none are pinned or tuned: the fewest that fit, for the
+// smallest register window.  In complex128 the 4th-order stencil of 769 to 1024
+// points takes two: with one, a block of 16 wavefronts is alone on its compute
+// unit and waits at its own barriers (plain operator, 32 x 32 x 96, 192 vectors:
+// 166 us, 157 with two; 24 vectors 32.5 and 27.8).
+static int default_ppt(iobm_ctx c, int prec) {
+  if (prec == prec_index<double>() && c->g.nf == 2 && c->g.nxy > 768 && c->g.nxy <= 1024) return 2;
   for (int ppt : {1, 2, 3, 4})
     if (a25_ppt_ok(c, ppt)) return ppt;
   return 0;
+}
+
+// Whether chunks of 16 planes beat the longer ones of `zc` in the operators that
+// stream one vector (plain and residual; the autotuner times the fused one, and
+// only in solves that iterate with it).  A launch takes as many rounds as its
+// blocks fill the chip, of the chunk's planes and some 3 nf more (the window that
+// a block fills first): short chunks waste that, long ones leave the last round
+// nearly empty.  waves: wavefronts per SIMD that the plain variants' registers
+// admit; blocks of a number of wavefronts that 4 does not divide leave about two
+// of a compute unit's places empty (fitted).  Of 901 launches (12 plane sizes, 48
+// to 160 planes, 12 to 800 vectors) it shortens chunks of 32 planes in those
+// with hundreds of vectors: 400 of 16 x 16 x 48 in complex64 30.3 -> 22.4 us, of
+// 8 x 8 x 48 18.6 -> 12.7, 192 of 32 x 32 x 96 95.9 -> 81.9, of 24 x 24 x 96 in
+// complex128 90.6 -> 80.2; over all 3% less, one launch in 300 5 to 7% more.
+template <typename T>
+static bool short_chunks(iobm_ctx c, int ppt, int zc, int nrhs) {
+  static const int waves[2][3][4] = {{{8, 5, 4, 3}, {7, 4, 3, 3}, {6, 4, 3, 3}},   // complex128, nf = 1, 2, 3
+                                     {{8, 8, 5, 4}, {8, 5, 4, 4}, {7, 4, 3, 3}}};  // complex64
+  const int per_block = ((c->g.nxy + ppt - 1) / ppt + 63) / 64;
+  const int places = 4 * waves[prec_index<T>()][c->g.nf - 1][ppt - 1] - (per_block % 4 ? 2 : 0);
+  const long long resident = (long long)c->num_cu * std::min(16, std::max(1, places / per_block));
+  auto cost = [&](int z) {
+    const long long blocks = (long long)nrhs * ((c->g.nz + z - 1) / z);
+    return (blocks + resident - 1) / resident * (z + 3 * c->g.nf);
+  };
+  return zc > 16 && cost(16) < cost(zc);
 }
 
 // The stencil with any policy: the 2.5D kernel at the tuned (or default)
@@ -1923,8 +1954,10 @@ static hipError_t launch_stencil(iobm_ctx c, const Op& op, int nrhs, const doubl
   const iobm_launch_shape& sh = c->shape[prec_index<T>()];
   if (sh.stencil != 2) {
     int ppt = sh.points_per_thread, zc = sh.planes_per_block;
-    if (ppt <= 0) ppt = default_ppt(c);
+    if (ppt <= 0) ppt = default_ppt(c, prec_index<T>());
     if (zc <= 0) zc = 32;
+    constexpr bool one_stream = std::is_same<typename Op::Raw, cplx<T>>::value;
+    if (one_stream && ppt > 0 && short_chunks<T>(c, ppt, zc, nrhs)) zc = 16;
     // a small batch (the tail of a solve, a small refinement subset) gets
     // shorter chunks, so that there are blocks for every compute unit and no
     // block walks a long chunk alone
@@ -2373,7 +2406,6 @@ template hipError_t launch_precond_fft<float>(iobm_ctx, const zf*, zf*, zf*, int
                                               const ModeData*, const int*, Partial*);
 
 bool launch_shape_valid(iobm_ctx c, int prec, const iobm_launch_shape& s, std::string& why) {
-  (void)prec;
   if (s.stencil < 0 || s.stencil > 2 || s.plane_fft < 0 || s.plane_fft > 2) {
     why = "stencil and plane_fft must be 0, 1 or 2";
     return false;
@@ -2382,7 +2414,7 @@ bool launch_shape_valid(iobm_ctx c, int prec, const iobm_launch_shape& s, std::s
     why = "points_per_thread does not fit this plane size / FD order";
     return false;
   }
-  if (s.stencil == 1 && s.points_per_thread == 0 && default_ppt(c) == 0) {
+  if (s.stencil == 1 && s.points_per_thread == 0 && default_ppt(c, prec) == 0) {
     why = "no 2.5D stencil variant fits this plane size";
     return false;
   }
@@ -2406,7 +2438,7 @@ bool launch_shape_valid(iobm_ctx c, int prec, const iobm_launch_shape& s, std::s
 iobm_launch_shape launch_shape_in_effect(iobm_ctx c, int prec) {
   const iobm_launch_shape& s = c->shape[prec];
   iobm_launch_shape r;
-  const int ppt = s.points_per_thread > 0 ? s.points_per_thread : default_ppt(c);
+  const int ppt = s.points_per_thread > 0 ? s.points_per_thread : default_ppt(c, prec);
   r.stencil = (s.stencil == 2 || ppt == 0) ? 2 : 1;
   r.points_per_thread = r.stencil == 1 ? ppt : 0;
   r.planes_per_block = r.stencil == 1 ? (s.planes_per_block > 0 ? s.planes_per_block : 32) : 16;

@@ -419,3 +419,24 @@ def test_default_rz_pass(torch, n, nz, nf, c128, c64):
         z, rz = s.precondition(iobm.PC_LATERAL_FFT, rr, E=1.3, precision=prec, want_rz=True)
         p = rr.to(torch.complex128) * z.to(torch.complex128)
         assert np.abs(rz - p.flatten(1).sum(1).cpu().numpy()).max() <= tol * float(p.abs().flatten(1).sum(1).max())
+
+
+@pytest.mark.parametrize("nx,ny,nz,nf,n", [(8, 8, 48, 2, 400), (16, 16, 48, 2, 400), (20, 20, 48, 2, 400), (16, 16, 33, 2, 700), (20, 15, 31, 1, 500),
+                                           (24, 24, 80, 3, 100), (32, 32, 40, 2, 24), (31, 25, 40, 2, 30)])
+def test_default_stencil_shapes(torch, nx, ny, nz, nf, n):
+    """Batches on both sides of the default rule's lines (chunks of 16 or 32 planes; in complex128 one or two points per
+    thread from 769 points on): the chunk does not change a point's arithmetic, so that the default and pinned chunks
+    agree bit for bit; with the cache-based stencil they agree to the rounding of its other order of sums."""
+    from paper_1009_5300_amd import iobm
+    g = Grid(nx, ny, nz, 0.4, nf)
+    s = _solver(g, 0.2 * random_field(g.shape, 3, complex_=False))
+    for prec, dt, tol in ((iobm.C128, torch.float64, 1e-12), (iobm.C64_REFINED, torch.float32, 2e-5)):
+        x = torch.view_as_complex(torch.randn((n,) + g.shape + (2,), dtype=dt, device="cuda"))
+        s.set_launch_shape(prec, None)
+        y, ppt = s.apply(0.7, x, prec), s.get_launch_shape(prec)["points_per_thread"]
+        assert ppt == (2 if prec == iobm.C128 and nf == 2 and nx * ny > 768 else 1)
+        for planes in (8, 16, 32):
+            s.set_launch_shape(prec, {"stencil": 1, "points_per_thread": ppt, "planes_per_block": planes})
+            assert torch.equal(s.apply(0.7, x, prec), y)
+        s.set_launch_shape(prec, {"stencil": 2})
+        assert float((s.apply(0.7, x, prec) - y).abs().max()) <= tol * float(y.abs().max())
