@@ -20,7 +20,6 @@ struct ModalScal {
   zd rho, sigma;          // r^T z and z^T q_old of the current residual
   zd rho_old, alpha_old;  // of the last step
   zd alpha;               // written by the mode pass of the step
-  double n2;              // |r|^2
   int step;               // index of the current residual since the last replacement
   int base;               // residuals before this one are folded into S and T
   int flag;               // breakdown

@@ -89,8 +89,8 @@ constexpr bool pm_sum(int mode) { return mode == PM_FULL || mode == PM_VFWD; }
 // of G threads takes them in two steps around a block barrier: NS strided
 // sums of each value into LDS (read at the kernel's start, beside the plane:
 // one thread adding them in turn would expose a load latency per block of
-// modes), then threads t < 6 write one field each.
-constexpr int kAdvValues = 5;
+// modes), then threads t < 5 write one field each.
+constexpr int kAdvValues = 4;  // rho and sigma (|r|^2 is read at a check only, k_modal_check)
 constexpr int adv_subs(int G) { return G / kAdvValues < 1 ? 1 : (G / kAdvValues > 16 ? 16 : G / kAdvValues); }
 template <int G>
 __device__ __forceinline__ void advance_sums(double* sub, const double* part, int nmb, int t) {
@@ -112,8 +112,7 @@ __device__ __forceinline__ void advance_scalars(ModalScal& s, const double* sub,
       case 0: s.rho_old.re = s.rho.re; s.rho.re = v; break;
       case 1: s.rho_old.im = s.rho.im; s.rho.im = v; break;
       case 2: s.sigma.re = v; break;
-      case 3: s.sigma.im = v; break;
-      default: s.n2 = v; break;
+      default: s.sigma.im = v; break;
     }
   } else if (t == kAdvValues) {
     s.alpha_old = s.alpha;
