@@ -581,8 +581,8 @@ def main():
     s = iobm.Solver(g.nx, g.ny, g.nz, g.spacings, g.nf)
     s.set_potential(w.V)
     opts = iobm.default_opts()
-    # one-time setup (not a step): allocation of the batch workspaces and the
-    # launch-shape autotuner, which runs inside the first solve
+    # one-time setup (not a step): allocation of the batch workspaces, inside
+    # the first solve
     torch.cuda.synchronize()
     t_setup = time.perf_counter()
     out = s.solve(w.energies, opts=opts)

@@ -279,9 +279,10 @@ __device__ __forceinline__ void add_nonlocal(const KBPlane<T>& kb, const cplx<T>
 // SPLIT N threads per plane: each thread (pair) transforms one row and then
 // one column in registers, the plane going through one padded LDS copy.
 // Bound: PM_FULL carries four line transforms per element against two
-// streams, so it is limited by vector arithmetic (about 5000 instructions
-// per wavefront and plane at N = 48) nearly as much as by memory.
-// Measured: 4.4 TB/s at 48 x 48 x 128 with 768 states, 0.54 ms per launch.
+// streams and is limited by vector arithmetic (complex64, N = 48: 4,340 vector
+// instructions per wavefront and plane, which take 92% of the SIMDs' issue
+// cycles over the launch), nearly as much by memory: 4.4 TB/s at 48 x 48 x 128
+// with 768 states, 0.54 ms per launch.
 template <typename T, int N, int PPB, int MODE>
 __global__ void __launch_bounds__((line_split<T, N>() * N * PPB)) __attribute__((amdgpu_waves_per_eu(2)))
     k_plane_reg(PlaneArgs<T> A) {
@@ -783,7 +784,8 @@ __device__ __forceinline__ void ring_coeffs(const zd* ha, const zd* hb, int base
 // MB modes x C chunks of one right-hand side (MB C <= 512).  The inputs of a step (W,
 // R, R_old) are each read once, the boundary planes of R' pass between
 // chunks through LDS.  Bound: memory (5 streams); the per-element work is
-// about 8 nf complex multiply-adds and three FP64 dot products.  Measured, with
+// about 8 nf complex multiply-adds and three FP64 dot products (59% of the issue
+// cycles at 48 x 48 x 128; wavefronts wait a third of theirs).  Measured, with
 // the starts and folds: 4.9 TB/s (48 x 48 x 128, 768 states), where the passes
 // it stands for (operator, residual update, z filter, r^T z) took 12 of the
 // operator-applying iteration's 14 streams; a solve there 68.7 -> 48.1 ms.

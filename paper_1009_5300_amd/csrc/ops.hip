@@ -2255,7 +2255,7 @@ hipError_t launch_fft_planes(iobm_ctx c, const cplx<T>* in, cplx<T>* out, int si
   return hipGetLastError();
 }
 
-// chunk length of the z filter (tuned per context and precision)
+// chunk length of the z filter (pinned, or the default rule)
 // With dpart (requires zfilter_dot_ok), the paired layout and the partials of
 // the bilinear form r^T z, dpart[rhs][0..nz).
 template <typename T>
@@ -2326,8 +2326,8 @@ static bool zfilter_dot_ok(iobm_ctx c) {
 
 template <typename T>
 static int zfilter_chunk(iobm_ctx c) {
-  const int tuned = c->shape[prec_index<T>()].zfilter_chunk;
-  return tuned > 0 ? tuned : default_zfilter_chunk(c);
+  const int pinned = c->shape[prec_index<T>()].zfilter_chunk;
+  return pinned > 0 ? pinned : default_zfilter_chunk(c);
 }
 
 template <typename T>
