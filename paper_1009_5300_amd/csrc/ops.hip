@@ -1932,7 +1932,7 @@ static int default_ppt(iobm_ctx c, int prec) {
 // complex128 90.6 -> 80.2; over all 3% less, one launch in 300 5 to 7% more.
 template <typename T>
 static bool short_chunks(iobm_ctx c, int ppt, int zc, int nrhs) {
-  static const int waves[2][3][4] = {{{8, 5, 4, 3}, {7, 4, 3, 3}, {6, 4, 3, 3}},   // complex128, nf = 1, 2, 3
+  static const int waves[2][3][4] = {{{8, 5, 4, 3}, {7, 4, 3, 3}, {5, 4, 3, 3}},   // complex128, nf = 1, 2, 3
                                      {{8, 8, 5, 4}, {8, 5, 4, 4}, {7, 4, 3, 3}}};  // complex64
   const int per_block = ((c->g.nxy + ppt - 1) / ppt + 63) / 64;
   const int places = 4 * waves[prec_index<T>()][c->g.nf - 1][ppt - 1] - (per_block % 4 ? 2 : 0);
